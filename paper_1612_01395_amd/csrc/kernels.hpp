@@ -38,34 +38,9 @@
 
 #include <type_traits>
 
+#include "method.hpp"
+
 namespace pbcgs {
-
-constexpr int kWG = 256;                  // threads per workgroup: 4 x wave64
-constexpr int kMaxD = 5;                  // dot products per reduction phase
-constexpr int kMaxR = 1024;               // 64-row blocks per wave (a power of two)
-constexpr int kLevels = 11;               // levels of a wave's pairwise tree: kMaxR = 2^(kLevels-1)
-constexpr int kMaxG = 1024;               // workgroups of a producing kernel
-constexpr int kChunk = kMaxG / kWG;       // partials per thread when consuming
-
-// DS_CHECK (precision form only): the binary32 recursive residual passed tol;
-// the host confirms with the binary64 true residual before declaring SUCCESS.
-enum : int32_t { DS_RUNNING = 0, DS_SUCCESS = 1, DS_BREAKDOWN = 2, DS_NONFINITE = 3, DS_CHECK = 4 };
-
-// Device-resident solver state: scalars of the method and the status word.
-struct alignas(128) DevState {
-  double alpha;   // alpha_i
-  double beta;    // beta_{i-1}
-  double omega;   // omega_{i-1} (omega_i once reduction 1 of iteration i is done)
-  double gamma;   // (r0, r_i)
-  double rho0;    // ||r_0||
-  double relres;  // last ||r_i|| / ||r_0||
-  double tol;
-  double result;  // output of utility reductions
-  int32_t status;
-  int32_t iters;  // completed x updates
-  int32_t n_rr;   // residual replacements done
-  int32_t pad[5];
-};
 
 // ---------------------------------------------------------------------------
 // Operators: apply one row of y = A x, summing in ascending column order.
@@ -1137,55 +1112,9 @@ __device__ __forceinline__ double apply_pc(const Args& a, int32_t row, double va
   return val;
 }
 
-// ---------------------------------------------------------------------------
-// Pairwise reduction machinery.
-// ---------------------------------------------------------------------------
-
-// 64-bit DPP move: lane l receives the value of the lane selected by CTRL in
-// the rows enabled by ROW_MASK; other lanes receive 0.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
-}
-
-template <int CTRL, int ROW_MASK, class T>
-__device__ __forceinline__ T dpp_t(T v) {
-  if constexpr (sizeof(T) == 8) return dpp_f64<CTRL, ROW_MASK>(v);
-  else return dpp_f32<CTRL, ROW_MASK>(v);
-}
-
-// Balanced-tree sum over the 64 lanes of a wave; the result is valid in lane
-// 63.  Level m adds to the last lane of every aligned block of 2m lanes the
-// sum held by the last lane of the block's left half (row_shr 1, 2, 4, 8,
-// then row_bcast 15 and 31 across the 16-lane rows), so lane 63 ends with
-// ((l0 + l1) + (l2 + l3)) + ... exactly as the pairwise order prescribes.
-template <int ND, class T>
-__device__ __forceinline__ void wave_sum63(T (&v)[ND]) {
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x111, 0xF>(v[k]);
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x112, 0xF>(v[k]);
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x114, 0xF>(v[k]);
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x118, 0xF>(v[k]);
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x142, 0xA>(v[k]);
-#pragma unroll
-  for (int k = 0; k < ND; ++k) v[k] = v[k] + dpp_t<0x143, 0xC>(v[k]);
-}
-
 // Balanced-tree sum of one value per thread over the workgroup (256 threads,
 // 4 waves); every thread receives the totals.  No barrier after the last read
-// of lw: a kernel gathers at most once per launch (its branches are
-// exclusive), and the persistent kernel's grid barrier separates its gathers.
+// of lw: a kernel gathers at most once per launch (its branches are exclusive).
 template <int ND, class T>
 __device__ __forceinline__ void wg_sum_all(T (&v)[ND], T (&out)[ND]) {
   __shared__ T lw[4][ND];
@@ -1293,8 +1222,7 @@ __device__ __forceinline__ void produce(const Args& a, Body body) {
     for (int k = 0; k < ND; ++k)
       a.pout[k * a.pstride + wg_index(a)] = double((wtot[k][0] + wtot[k][1]) + (wtot[k][2] + wtot[k][3]));
   }
-  // no barrier here: a kernel produces once per launch, and the persistent
-  // kernel's grid barrier separates its reductions
+  // no barrier here: a kernel produces once per launch
 }
 
 // As produce(), with each lane taking two neighbouring rows: lane l of a
@@ -1485,144 +1413,8 @@ __device__ __forceinline__ void each_row(const Args& a, Body body) {
   }
 }
 
-__device__ __forceinline__ bool finite(double v) { return __builtin_isfinite(v); }
-__device__ __forceinline__ bool leader() { return blockIdx.x == 0 && threadIdx.x == 0; }
-
-// Register copy of the state (field by field: no aligned aggregate on the stack).
-struct State {
-  double alpha, beta, omega, gamma, rho0, relres, tol, result;
-  int32_t status, iters, n_rr;
-};
-
-__device__ __forceinline__ State load_state(const DevState* p) {
-  State s;
-  s.alpha = p->alpha; s.beta = p->beta; s.omega = p->omega; s.gamma = p->gamma;
-  s.rho0 = p->rho0; s.relres = p->relres; s.tol = p->tol; s.result = p->result;
-  s.status = p->status; s.iters = p->iters; s.n_rr = p->n_rr;
-  return s;
-}
-
 __device__ __forceinline__ void publish(const Args& a, const State& s) {
-  if (sys_leader(a)) {
-    DevState* p = a.sout;
-    p->alpha = s.alpha; p->beta = s.beta; p->omega = s.omega; p->gamma = s.gamma;
-    p->rho0 = s.rho0; p->relres = s.relres; p->tol = s.tol; p->result = s.result;
-    p->status = s.status; p->iters = s.iters; p->n_rr = s.n_rr;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Scalar steps of the method.  Every thread evaluates them on identical
-// inputs; only the leader writes the history.
-// ---------------------------------------------------------------------------
-
-// gamma = (r0, r0), rho0 = ||r0|| (the setup of Algorithms 7-11).
-__device__ __forceinline__ void fin_setup_gamma(State& s, double* hist, double g) {
-  s.gamma = g;
-  const double rho0 = sqrt(g);
-  s.rho0 = rho0;
-  s.relres = 1.0;
-  if (hist && leader()) hist[0] = 1.0;
-  if (!finite(rho0)) s.status = DS_NONFINITE;
-  else if (rho0 == 0.0) { s.status = DS_SUCCESS; s.relres = 0.0; }
-}
-
-// alpha_0 = (r0, r0) / (r0, w0), beta_{-1} = omega_{-1} = 0 (the setup of Algorithms 9 and 11).
-__device__ __forceinline__ void fin_setup_alpha(State& s, double delta) {
-  if (!finite(delta)) { s.status = DS_NONFINITE; return; }
-  if (delta == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double alpha = s.gamma / delta;
-  if (!finite(alpha)) { s.status = DS_NONFINITE; return; }
-  s.alpha = alpha;
-  s.beta = 0.0;
-  s.omega = 0.0;
-}
-
-// omega_i = (q, y) / (y, y)  (reduction 1 of Algorithms 7, 9, 10 and 11).
-// Returns true when (y, y) = 0: then q = 0
-// and x_i + alpha_i p^_i is the solution; the caller applies that update.
-__device__ __forceinline__ bool fin_omega(State& s, double* hist, double qy, double yy) {
-  if (!finite(qy) || !finite(yy)) { s.status = DS_NONFINITE; return false; }
-  if (yy == 0.0) {
-    s.iters += 1;
-    s.relres = 0.0;
-    if (hist && leader()) hist[s.iters] = 0.0;
-    s.status = DS_SUCCESS;
-    return true;
-  }
-  const double omega = qy / yy;
-  if (!finite(omega)) { s.status = DS_NONFINITE; return false; }
-  s.omega = omega;
-  return false;
-}
-
-// alpha_{i+1} of the pipelined solvers from gamma' = (r0, r_{i+1}), eta = (r0, w_{i+1}),
-// sigma_s = (r0, s_i), sigma_z = (r0, z_i): eq. (3) is gamma' / (eta + beta sigma_s
-// - beta omega sigma_z); eq. (5) is the same quantity rearranged so that sigma_s
-// drops out, (1/omega + eta/gamma' - (beta omega) (sigma_z/gamma'))^{-1}.  Both
-// evaluate in the order and grouping the equations write, without contraction.
-__device__ __forceinline__ void next_alpha(State& s, int32_t aform, double g1, double eta, double sig_s,
-                                           double sig_z, double beta, double omega) {
-  double an;
-  if (aform == 5) {
-    if (g1 == 0.0) { s.status = DS_BREAKDOWN; return; }
-    const double den = (1.0 / omega + eta / g1) - (beta * omega) * (sig_z / g1);
-    if (den == 0.0) { s.status = DS_BREAKDOWN; return; }
-    an = 1.0 / den;
-  } else {
-    const double den = eta + beta * sig_s - beta * omega * sig_z;
-    if (den == 0.0 || g1 == 0.0) { s.status = DS_BREAKDOWN; return; }
-    an = g1 / den;
-  }
-  if (!finite(an)) { s.status = DS_NONFINITE; return; }
-  s.alpha = an;
-  s.gamma = g1;
-}
-
-// Reduction 2 of p-BiCGStab: stopping test, beta_i and alpha_{i+1} by eq. (3)
-// or eq. (5) (Algorithm 9, Algorithm 11).
-__device__ __forceinline__ void fin_pipe_b(State& s, double* hist, const double (&d)[5], int32_t aform) {
-  const double g1 = d[0], eta = d[1], sig_s = d[2], sig_z = d[3], nu = d[4];
-  s.iters += 1;
-  if (!finite(g1) || !finite(eta) || !finite(sig_s) || !finite(sig_z) || !finite(nu)) {
-    s.status = DS_NONFINITE;
-    return;
-  }
-  const double relres = sqrt(nu) / s.rho0;
-  s.relres = relres;
-  if (hist && leader()) hist[s.iters] = relres;
-  if (relres <= s.tol) { s.status = DS_SUCCESS; return; }
-  const double alpha = s.alpha, omega = s.omega, gamma = s.gamma;
-  if (omega == 0.0 || gamma == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double beta = (alpha / omega) * (g1 / gamma);
-  if (!finite(beta)) { s.status = DS_NONFINITE; return; }
-  s.beta = beta;
-  next_alpha(s, aform, g1, eta, sig_s, sig_z, beta, omega);
-}
-
-// alpha_i = (r0, r_i) / (r0, s_i)  (the first reduction of Algorithm 7).
-__device__ __forceinline__ void fin_bicg_alpha(State& s, double delta) {
-  if (!finite(delta)) { s.status = DS_NONFINITE; return; }
-  if (delta == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double alpha = s.gamma / delta;
-  if (!finite(alpha)) { s.status = DS_NONFINITE; return; }
-  s.alpha = alpha;
-}
-
-// Stopping test and beta_i = (alpha/omega) (r0, r_{i+1}) / (r0, r_i)  (the last reduction of Algorithm 7).
-__device__ __forceinline__ void fin_bicg_beta(State& s, double* hist, double g1, double nu) {
-  s.iters += 1;
-  if (!finite(g1) || !finite(nu)) { s.status = DS_NONFINITE; return; }
-  const double relres = sqrt(nu) / s.rho0;
-  s.relres = relres;
-  if (hist && leader()) hist[s.iters] = relres;
-  if (relres <= s.tol) { s.status = DS_SUCCESS; return; }
-  const double alpha = s.alpha, omega = s.omega, gamma = s.gamma;
-  if (omega == 0.0 || gamma == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double beta = (alpha / omega) * (g1 / gamma);
-  if (!finite(beta)) { s.status = DS_NONFINITE; return; }
-  s.beta = beta;
-  s.gamma = g1;
+  if (sys_leader(a)) store_state(a.sout, s);
 }
 
 // Reads the incoming state; a stopped solve is passed through unchanged.
@@ -2012,44 +1804,6 @@ __global__ __launch_bounds__(kWG) void k_ca_w(Op op, Args a) { d_ca_w<Op>(op, a)
 //   Algorithm 6 (p-CG): alpha, beta ; n = A M^{-1} w and every recurrence -- one.
 // ===========================================================================
 
-// First reduction of Algorithms 4 and 6: rho0 = sqrt(nu_0), alpha_0 = gamma_0 / delta_0, beta_0 = 0.
-__device__ __forceinline__ void fin_cgs_first(State& s, double* hist, const double (&d)[3]) {
-  const double gamma = d[0], delta = d[1], nu = d[2];
-  s.relres = 1.0;
-  if (hist && leader()) hist[0] = 1.0;
-  if (!finite(gamma) || !finite(delta) || !finite(nu)) { s.status = DS_NONFINITE; return; }
-  const double rho0 = sqrt(nu);
-  s.rho0 = rho0;
-  if (rho0 == 0.0) { s.status = DS_SUCCESS; s.relres = 0.0; return; }
-  if (delta == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double alpha = gamma / delta;
-  if (!finite(alpha)) { s.status = DS_NONFINITE; return; }
-  s.alpha = alpha;
-  s.beta = 0.0;
-  s.gamma = gamma;
-}
-
-// Later reductions of Algorithms 4 and 6: stopping test on ||r_i|| (i = s.iters),
-// beta_i = gamma_i / gamma_{i-1}, alpha_i = (delta / gamma_i - beta_i / alpha_{i-1})^{-1}.
-__device__ __forceinline__ void fin_cgs_next(State& s, double* hist, const double (&d)[3]) {
-  const double g1 = d[0], delta = d[1], nu = d[2];
-  if (!finite(g1) || !finite(delta) || !finite(nu)) { s.status = DS_NONFINITE; return; }
-  const double relres = sqrt(nu) / s.rho0;
-  s.relres = relres;
-  if (hist && leader()) hist[s.iters] = relres;
-  if (relres <= s.tol) { s.status = DS_SUCCESS; return; }
-  if (s.gamma == 0.0 || g1 == 0.0 || s.alpha == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double beta = g1 / s.gamma;
-  if (!finite(beta)) { s.status = DS_NONFINITE; return; }
-  const double den = delta / g1 - beta / s.alpha;
-  if (den == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double alpha = 1.0 / den;
-  if (!finite(alpha)) { s.status = DS_NONFINITE; return; }
-  s.beta = beta;
-  s.alpha = alpha;
-  s.gamma = g1;
-}
-
 // Setup of Algorithm 2: r = b - A x ; u = M^{-1} r ; p = u ; partials (r, r), (r, u).
 // ONEPHASE (Algorithms 4 and 6): no p; p = s = z = q = 0 instead.
 template <class Op, int PC, bool ONEPHASE>
@@ -2143,14 +1897,7 @@ __device__ __forceinline__ void d_cg_b(Args a) {
   PBCGS_PROLOGUE(st)
   double g[1];
   gather_sums<1>(a, g);
-  const double delta = g[0];
-  if (!finite(delta)) st.status = DS_NONFINITE;
-  else if (delta == 0.0) st.status = DS_BREAKDOWN;
-  else {
-    const double alpha = st.gamma / delta;
-    if (!finite(alpha)) st.status = DS_NONFINITE;
-    else st.alpha = alpha;
-  }
+  fin_cg_alpha(st, g[0]);
   publish(a, st);
   if (st.status != DS_RUNNING) return;
   const double alpha = st.alpha;
@@ -2168,22 +1915,6 @@ __device__ __forceinline__ void d_cg_b(Args a) {
 }
 template <int PC>
 __global__ __launch_bounds__(kWG) void k_cg_b(Args a) { d_cg_b<PC>(a); }
-
-// Algorithm 2, kernel 3: stopping test, beta = (r', u') / (r, u) ; p = u + beta p.
-__device__ __forceinline__ void fin_cg_beta(State& s, double* hist, const double (&d)[2]) {
-  const double g1 = d[0], nu = d[1];
-  s.iters += 1;
-  if (!finite(g1) || !finite(nu)) { s.status = DS_NONFINITE; return; }
-  const double relres = sqrt(nu) / s.rho0;
-  s.relres = relres;
-  if (hist && leader()) hist[s.iters] = relres;
-  if (relres <= s.tol) { s.status = DS_SUCCESS; return; }
-  if (s.gamma == 0.0) { s.status = DS_BREAKDOWN; return; }
-  const double beta = g1 / s.gamma;
-  if (!finite(beta)) { s.status = DS_NONFINITE; return; }
-  s.beta = beta;
-  s.gamma = g1;
-}
 
 template <int PC>
 __device__ __forceinline__ void d_cg_c(Args a) {
@@ -4122,153 +3853,5 @@ __global__ void kb_init_state(const SysDesc* sys, int32_t nsys, int32_t slot, do
   for (int j = 0; j < 5; ++j) st->pad[j] = 0;
 }
 #undef PBCGS_BIND_WG
-
-// ===========================================================================
-// Persistent form for small systems: the whole solve in one cooperative
-// launch.  The phases are those of the graph schedule (the same device
-// bodies, state ring and partial-sum buffers); a grid barrier replaces each
-// kernel boundary.  Every wait is bounded: a barrier that does not complete
-// in about a quarter of a second sets an error flag and the kernel ends.
-// ===========================================================================
-struct GridBar {
-  unsigned cnt;   // arrivals at the current barrier
-  unsigned gen;   // completed barriers
-  int err;        // set when a wait timed out
-  int pad;
-};
-
-// Partial-sum buffers by role (the same roles as the launches of the driver).
-enum : int { PBR_SETUP1 = 0, PBR_SETUP2, PBR_A, PBR_B, PBR_B1, PBR_B3, PBR_B4 };
-
-struct PersistCfg {
-  DevState* st;      // the two-slot state ring
-  double* parts;     // partial-sum buffers, kMaxD * kMaxG doubles per role
-  GridBar* bar;
-  int64_t* qout;     // phases run (the state is in slot qout & 1 at the end)
-  int32_t variant;   // 0 BiCGStab, 1 p-BiCGStab, 2 p-BiCGStab with replacement
-  int32_t rr_period, rr_max, maxit;
-};
-
-// Grid-wide barrier with release/acquire at agent scope; false after a timeout.
-__device__ __forceinline__ bool grid_sync(GridBar* b, unsigned nwg) {
-  __shared__ int ok_;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int ok = 1;
-    const unsigned g = __hip_atomic_load(&b->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    const unsigned prev = atomicAdd(&b->cnt, 1u);
-    if (prev == nwg - 1) {
-      atomicExch(&b->cnt, 0u);
-      __threadfence();
-      atomicAdd(&b->gen, 1u);
-    } else {
-      unsigned spins = 0;
-      while (__hip_atomic_load(&b->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g) {
-        __builtin_amdgcn_s_sleep(2);
-        if (++spins > (1u << 22)) {
-          atomicOr(&b->err, 1);
-          ok = 0;
-          break;
-        }
-      }
-    }
-    if (__hip_atomic_load(&b->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) ok = 0;
-    __threadfence();
-    ok_ = ok;
-  }
-  __syncthreads();
-  return ok_ != 0;
-}
-
-__device__ __forceinline__ bool rr_due_dev(const PersistCfg& c, int64_t i) {
-  if (c.variant != 2 || c.rr_period <= 0 || i < 0) return false;
-  if ((i + 1) % c.rr_period != 0) return false;
-  const int64_t before = (i + 1) / c.rr_period - 1;
-  return c.rr_max < 0 || before < c.rr_max;
-}
-
-template <class Op, int PC>
-__global__ __launch_bounds__(kWG) void k_persist(Op op, Args base, PersistCfg c) {
-  int64_t q = 0;
-  const unsigned nwg = gridDim.x;
-  bool ok = true;
-  auto L = [&](int pin, int pout, bool first) {
-    Args a = base;
-    a.wg = -1;
-    a.sin = c.st + (q & 1);
-    a.sout = c.st + ((q + 1) & 1);
-    a.pin = pin >= 0 ? c.parts + (size_t)pin * kMaxD * kMaxG : nullptr;
-    a.pout = pout >= 0 ? c.parts + (size_t)pout * kMaxD * kMaxG : nullptr;
-    a.Gin = base.G;
-    a.first = first ? 1 : 0;
-    ++q;
-    return a;
-  };
-  auto sync = [&]() {
-    if (ok) ok = grid_sync(c.bar, nwg);
-    return ok;
-  };
-  const bool pipe = c.variant != 0;
-  if (pipe) {
-    d_setup_r0<Op, PC, true>(op, L(-1, PBR_SETUP1, false));
-    if (sync()) d_setup_w0<Op, PC>(op, L(PBR_SETUP1, PBR_SETUP2, false));
-  } else {
-    d_setup_r0<Op, PC, false>(op, L(-1, PBR_SETUP1, false));
-  }
-  sync();
-  int64_t i = 0;
-  for (; ok && i < c.maxit; ++i) {
-    if (!pipe) {
-      d_b1<Op, PC>(op, L(PBR_SETUP1, PBR_B1, i == 0));
-      if (sync()) d_b2<PC>(L(PBR_B1, -1, false));
-      if (sync()) d_b3<Op, PC>(op, L(-1, PBR_B3, false));
-      if (sync()) d_b4<PC>(L(PBR_B3, PBR_B4, false));
-      if (sync()) d_b5<PC>(L(PBR_B4, -1, false));
-      sync();
-    } else {
-      if (rr_due_dev(c, i - 1)) {
-        d_rr_p<PC>(L(PBR_B, -1, false));
-        if (sync()) d_rr_s<Op, PC>(op, L(-1, -1, false));
-        if (sync()) d_pa<Op, PC, true>(op, L(-1, PBR_A, false));
-      } else {
-        d_pa<Op, PC, false>(op, L(i == 0 ? PBR_SETUP2 : PBR_B, PBR_A, i == 0));
-      }
-      sync();
-      if (ok && rr_due_dev(c, i)) {
-        d_rr_x<PC>(L(PBR_A, -1, false));
-        if (sync()) d_rr_r<Op, PC>(op, L(-1, -1, false));
-        if (sync()) d_rr_w<Op, PC>(op, L(-1, PBR_B, false));
-      } else if (ok) {
-        d_pb<Op, PC>(op, L(PBR_A, PBR_B, false));
-      }
-      sync();
-    }
-    if (!ok) break;
-    // the state after this iteration, published before the barrier
-    const int32_t status = __hip_atomic_load(&c.st[q & 1].status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (status != DS_RUNNING) break;
-  }
-  // maxit reached: the reduction left pending by the last phase, in workgroup 0
-  if (ok && i == c.maxit) {
-    if (pipe) {
-      const Args a = (c.maxit == 0) ? L(PBR_SETUP2, -1, false) : L(PBR_B, -1, false);
-      if (blockIdx.x == 0) {
-        Args a0 = a;
-        a0.wg = 0;
-        if (c.maxit == 0) d_finish<1>(a0);
-        else d_finish<0>(a0);
-      }
-    } else if (c.maxit == 0) {
-      const Args a = L(PBR_SETUP1, -1, false);
-      if (blockIdx.x == 0) {
-        Args a0 = a;
-        a0.wg = 0;
-        d_finish<2>(a0);
-      }
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *c.qout = q;
-}
 
 }  // namespace pbcgs

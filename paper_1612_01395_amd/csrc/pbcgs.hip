@@ -17,6 +17,7 @@
 #include "../../include/pbcgs.h"
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "resident.h"
 #include "debug.hpp"
 
 using namespace pbcgs;
@@ -93,9 +94,8 @@ struct pbcgs_ctx_s {
   DevState* st = nullptr;   // state slots (device): 0, 1 solver ring; 2, 3 utility reductions
   DevState* hst = nullptr;  // pinned host copies: slots 0, 1 for polling, 2 for reads of a state or a scalar
   int32_t* flag = nullptr;  // structural error flags of utility kernels
-  GridBar* bar = nullptr;   // grid barrier of the persistent form
-  int64_t* qout = nullptr;  // phases run by the persistent form
   int coop = -1;            // device supports cooperative launches (-1: not asked yet)
+  unsigned char* res = nullptr;  // resident solves: exchange words, then kResAux bytes
   int32_t* hflag = nullptr; // pinned host copy
   double* part = nullptr;   // PB_COUNT buffers of kMaxD * kMaxG partial sums
   double* ws = nullptr;     // solver vectors
@@ -138,6 +138,7 @@ struct pbcgs_ctx_s {
   bool poison = false;
   int32_t perturb_iter = -1;
   double perturb_scale = 1.0;
+  int cus = 0;         // compute units of the device
   std::string devkey;  // "<architecture> <compute units>cu": the device part of launch-shape cache keys
 };
 
@@ -976,71 +977,7 @@ struct Driver {
     return PBCGS_SUCCESS;
   }
 
-  // The persistent form (binary64, no per-kernel timing), on request only
-  // (PBCGS_PERSIST=1): measured on MI355X, a grid barrier -- an agent-scope
-  // release per workgroup, which writes back the per-XCD L2 caches -- costs
-  // more than a kernel boundary between graph-launched kernels, and more the
-  // larger the grid, so the graph schedule is the default at every size.
-  bool use_persistent() {
-    if constexpr (MP) return false;
-    if (ctx->noalloc) return false;
-    if (o.flags & 2) return false;
-    if (o.variant >= PBCGS_CA_BICGSTAB) return false;
-    if (o.maxit > 200000) return false;
-    if (ctx->perturb_iter >= 0) return false;
-    if (env_int("PBCGS_PERSIST", 0) != 1) return false;
-    if (ctx->coop < 0) {
-      int v = 0;
-      ctx->coop = (hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && v) ? 1 : 0;
-    }
-    if (ctx->coop != 1) return false;
-    // every workgroup must be resident at once
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_persist<Op, PC>), kWG,
-                                                     0) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
-      return false;
-    return (int64_t)a.G <= (int64_t)per_cu * cus;
-  }
-
-  int run_persistent(pbcgs_info* info) {
-    hipStream_t s = ctx->stream;
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
-    k_init_state<<<1, 64, 0, s>>>(ctx->st, o.tol);
-    HIP_TRY(ctx, hipMemsetAsync(ctx->bar, 0, sizeof(GridBar), s));
-    PersistCfg c;
-    c.st = ctx->st;
-    c.parts = ctx->part;
-    c.bar = ctx->bar;
-    c.qout = ctx->qout;
-    c.variant = o.variant;
-    c.rr_period = o.rr_period;
-    c.rr_max = o.rr_max;
-    c.maxit = o.maxit;
-    Args base = a;
-    void* args[] = {&op, &base, &c};
-    HIP_TRY(ctx, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_persist<Op, PC>), dim3((unsigned)a.G),
-                                            dim3(kWG), args, 0, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_stop, s));
-    GridBar hb;
-    int64_t hq = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&hb, ctx->bar, sizeof hb, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(&hq, ctx->qout, sizeof hq, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (hb.err) return fail(ctx, PBCGS_ERR_HIP, "persistent solve: a grid barrier timed out");
-    q = hq;
-    DevState fin;
-    int rc = read_state(ctx, (int)(q & 1), &fin);
-    if (rc != PBCGS_SUCCESS) return rc;
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop);
-    return report(info, fin, ms);
-  }
-
   int run(pbcgs_info* info) {
-    if constexpr (!MP) {  // the precision form has no persistent kernel (and instantiates none)
-      if (use_persistent()) return run_persistent(info);
-    }
     // graphs are instantiated (allocated) on first use: never without allocation
     const bool use_graph = !(o.flags & 1) && !(o.flags & 2) && !ctx->noalloc && ctx->perturb_iter < 0;
     timing = (o.flags & 2) != 0 && !ctx->noalloc;
@@ -1163,6 +1100,140 @@ struct Driver {
     return info->status;
   }
 };
+
+// ---------------------------------------------------------------------------
+// Resident solves (resident.hpp).
+// ---------------------------------------------------------------------------
+// Whether a solve may take the resident form: a binary64 method it implements
+// on an operator of few diagonals, launched as the library chooses.  Options
+// and switches that ask for the streamed kernels (direct launches, kernel
+// timing, the CSR arrays, a launch shape or a kernel form from the
+// environment), the perturbation hook and the allocation-free entry point keep
+// those.  PBCGS_PERSIST=0 never takes the resident form, =1 also with the
+// environment's switches set.
+bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o) {
+  if (ctx->noalloc || ctx->perturb_iter >= 0 || o.precision != PBCGS_FP64 || (o.flags & (1 | 2 | 8 | 16))) return false;
+  if (!res_method(o.variant) || o.maxit > 100000000) return false;  // exchange numbers stay in 32 bits
+  const bool layout = A->kind == OP_CSR && A->ndia > 0 && A->ndia <= kResMaxND;
+  if (!layout && A->kind != OP_ST5 && A->kind != OP_ST7) return false;
+  const int mode = env_int("PBCGS_PERSIST", -1);
+  if (mode == 0) return false;
+  if (mode < 0) {
+    for (const char* e : {"PBCGS_R", "PBCGS_GTARGET", "PBCGS_VALUE_CODES", "PBCGS_XCD_MAP", "PBCGS_TWO_ROWS64",
+                          "PBCGS_DIA_CACHED"})
+      if (std::getenv(e)) return false;
+  }
+  if (ctx->coop < 0) {
+    int v = 0;
+    ctx->coop = (hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && v) ? 1 : 0;
+  }
+  return ctx->coop == 1;
+}
+
+// The operator's structure in the resident form (values left out).
+ResOp resident_structure(const pbcgs_op_s* A) {
+  ResOp r;
+  std::memset(&r, 0, sizeof r);
+  r.n = A->n;
+  r.ld = (int32_t)padded(A->n);
+  if (A->kind == OP_CSR) {
+    r.mask = A->dmask;
+    r.nd = A->ndia;
+    for (int d = 0; d < r.nd; ++d) r.off[d] = A->dia_off[d];
+    return r;
+  }
+  r.nx = A->nx;
+  r.ny = A->ny;
+  r.nz = A->nz;
+  const int32_t nx = A->nx, nxy = A->nx * A->ny;
+  if (A->kind == OP_ST5) {
+    r.nd = 5;
+    const int32_t off[5] = {-nx, -1, 0, 1, nx};
+    std::memcpy(r.off, off, sizeof off);
+  } else {
+    r.nd = 7;
+    const int32_t off[7] = {-nxy, -nx, -1, 0, 1, nx, nxy};
+    std::memcpy(r.off, off, sizeof off);
+  }
+  return r;
+}
+
+// One value per diagonal of the CSR operator (of A M^{-1} when folded)?  Then
+// they go into op->c.  One host synchronisation.
+int resident_uniform(pbcgs_ctx_t ctx, const pbcgs_op_s* A, int pc_fold, const double* dv, double ds, ResOp* op,
+                     bool* uniform) {
+  unsigned char* aux = ctx->res + kResWords * sizeof(unsigned long long);
+  HIP_TRY(ctx, res_uniform(*op, A->rp, A->ci, A->va, pc_fold == PC_VEC ? dv : nullptr, pc_fold == PC_NONE, ds, aux,
+                           ctx->stream));
+  static_assert(sizeof(DevState) >= kResAux, "the pinned slot holds the result");
+  HIP_TRY(ctx, hipMemcpyAsync(&ctx->hst[2], aux, kResAux, hipMemcpyDeviceToHost, ctx->stream));
+  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  const unsigned char* h = reinterpret_cast<const unsigned char*>(&ctx->hst[2]);
+  int32_t flag;
+  std::memcpy(&flag, h + 8 * kResMaxND, sizeof flag);
+  *uniform = flag == 0;
+  if (*uniform) std::memcpy(op->c, h, sizeof(double) * op->nd);
+  return PBCGS_SUCCESS;
+}
+
+// Runs the solve from x_0 (its folded form y_0 when `fold` is set, see
+// k_fold_x) and leaves the iterate in ctx->ws; *done = false, with nothing of
+// the caller's written, when it did not run to its end (a launch refused, or a
+// wait that timed out because the device was busy for about a second).
+int run_resident(pbcgs_ctx_t ctx, const ResPlan& plan, const ResOp& op, const Args& a, const pbcgs_opts& o, int pc,
+                 const double* fold_dv, double fold_ds, bool fold, pbcgs_info* info, double* rho0, bool* done) {
+  hipStream_t s = ctx->stream;
+  *done = false;
+  ResJob j;
+  j.variant = o.variant;
+  j.rr_period = o.rr_period;
+  j.rr_max = o.rr_max;
+  j.maxit = o.maxit;
+  j.aform = alpha_form(o);
+  j.tol = o.tol;
+  j.pc = pc != PC_NONE;
+  j.dinv = pc == PC_VEC ? a.dinv : nullptr;
+  j.dinv_s = a.dinv_s;
+  j.b = a.b;
+  j.x0 = a.x;
+  j.hist = a.hist;
+  j.vecs = ctx->ws;
+  j.stride = (int64_t)padded(a.n) + (int64_t)kResVecPad;  // kResVecs of them fit the 14 workspace vectors' first 13
+  j.words = reinterpret_cast<unsigned long long*>(ctx->res);
+  j.err = &ctx->st[0].pad[0];
+  j.st = ctx->st;
+  HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
+  if (fold) {
+    const int xg = (a.n + kWG - 1) / kWG;
+    HIP_TRY(ctx, hipMemcpyAsync(res_x(j), a.x, sizeof(double) * (size_t)a.n, hipMemcpyDeviceToDevice, s));
+    if (fold_dv) k_fold_x<PC_VEC, true><<<xg, kWG, 0, s>>>(a.n, res_x(j), fold_dv, fold_ds);
+    else k_fold_x<PC_SCALAR, true><<<xg, kWG, 0, s>>>(a.n, res_x(j), fold_dv, fold_ds);
+    j.x0 = res_x(j);
+  }
+  if (res_launch(plan, op, j, s) != hipSuccess) {
+    (void)hipGetLastError();
+    return PBCGS_SUCCESS;
+  }
+  HIP_TRY(ctx, hipEventRecord(ctx->ev_stop, s));
+  DevState fin;
+  const int rc = read_state(ctx, 0, &fin);
+  if (rc != PBCGS_SUCCESS) return rc;
+  if (fin.pad[0] != 0 || fin.status < 0) return PBCGS_SUCCESS;
+  HIP_TRY(ctx, hipMemcpyAsync(a.x, res_x(j), sizeof(double) * (size_t)a.n, hipMemcpyDeviceToDevice, s));
+  float ms = 0.f;
+  (void)hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop);
+  info->iters = fin.iters;
+  info->n_rr = fin.n_rr;
+  info->status = map_status(fin.status);
+  info->syncs_per_iter = syncs_per_iteration(o.variant);
+  info->relres_rec = fin.relres;
+  info->ms = ms;
+  info->rows_per_wave_blocks = a.R;  // of the launches around it
+  info->workgroups = a.G;
+  *rho0 = fin.rho0;
+  *done = true;
+  return PBCGS_SUCCESS;
+}
 
 // Graph keys hold the bytes of the operator and argument structs, so these
 // structs must have no padding (whose contents would be indeterminate).
@@ -1585,8 +1656,7 @@ int pbcgs_ctx_create(int device, void* hip_stream, pbcgs_ctx_t* out) {
   bool ok = hipMalloc(&c->st, 4 * sizeof(DevState)) == hipSuccess &&
             hipMalloc(&c->part, sizeof(double) * kMaxD * kMaxG * PB_COUNT) == hipSuccess &&
             hipMalloc(&c->flag, 64) == hipSuccess &&
-            hipMalloc(&c->bar, sizeof(GridBar)) == hipSuccess &&
-            hipMalloc(&c->qout, sizeof(int64_t)) == hipSuccess &&
+            hipMalloc(&c->res, kResWords * sizeof(unsigned long long) + kResAux) == hipSuccess &&
             hipHostMalloc(&c->hst, 3 * sizeof(DevState), hipHostMallocDefault) == hipSuccess &&
             hipHostMalloc(&c->hflag, 64, hipHostMallocDefault) == hipSuccess &&
             hipEventCreate(&c->ev_start) == hipSuccess && hipEventCreate(&c->ev_stop) == hipSuccess &&
@@ -1605,10 +1675,12 @@ int pbcgs_ctx_create(int device, void* hip_stream, pbcgs_ctx_t* out) {
     return fail(nullptr, PBCGS_ERR_HIP, "context initialisation failed");
   }
   hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, device) == hipSuccess)
+  if (hipGetDeviceProperties(&prop, device) == hipSuccess) {
+    c->cus = prop.multiProcessorCount;
     c->devkey = std::string(prop.gcnArchName) + " " + std::to_string(prop.multiProcessorCount) + "cu";
-  else
+  } else {
     c->devkey = "device" + std::to_string(device);
+  }
   *out = c;
   return PBCGS_SUCCESS;
 }
@@ -1649,8 +1721,7 @@ int pbcgs_ctx_destroy(pbcgs_ctx_t ctx) {
   if (ctx->bhst) (void)hipHostFree(ctx->bhst);
   if (ctx->part) (void)hipFree(ctx->part);
   if (ctx->flag) (void)hipFree(ctx->flag);
-  if (ctx->bar) (void)hipFree(ctx->bar);
-  if (ctx->qout) (void)hipFree(ctx->qout);
+  if (ctx->res) (void)hipFree(ctx->res);
   if (ctx->st) (void)hipFree(ctx->st);
   if (ctx->hst) (void)hipHostFree(ctx->hst);
   if (ctx->hflag) (void)hipHostFree(ctx->hflag);
@@ -2266,6 +2337,52 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
     a.wh = hat ? v[9] : a.w;
     a.sh = hat ? v[10] : a.s;
     a.zh = hat ? v[11] : a.z;
+  }
+
+  if (resident_allowed(ctx, A, o)) {
+    const int pcl = folded ? PC_NONE : pc;  // Jacobi applied as written
+    const double ds = a.dinv_s;
+    const double* fdv = (folded && pc == PC_VEC) ? dinv_vec : nullptr;
+    ResOp rop = resident_structure(A);
+    ResPlan plan = res_plan(rop, o.variant, pcl != PC_NONE, ctx->cus);
+    bool uniform = true;
+    if (A->kind != OP_CSR) {
+      for (int d = 0; d < rop.nd; ++d) rop.c[d] = folded ? A->coef[d] * ds : A->coef[d];
+    } else if (plan.K > 0) {
+      rc = resident_uniform(ctx, A, folded ? pc : PC_NONE, fdv, ds, &rop, &uniform);
+      if (rc != PBCGS_SUCCESS) return rc;
+    }
+    if (plan.K > 0 && !uniform) {
+      // varying values are read from the layout each time: where the solve
+      // would read them as codes (2^18 rows and more) those are the better form
+      if (A->n < kViMinRows) {
+        DiaOp dop;
+        rc = dia_operator<double>(ctx, A, folded ? pc : PC_NONE, fdv, ds, &dop);
+        if (rc != PBCGS_SUCCESS) return rc;
+        rop.va = dop.va;
+        plan = res_plan(rop, o.variant, pcl != PC_NONE, ctx->cus);
+      } else {
+        plan.K = 0;
+      }
+    }
+    if (plan.K > 0) {
+      bool done = false;
+      double rho0 = 0.0;
+      rc = run_resident(ctx, plan, rop, a, o, pcl, fdv, ds, folded, info, &rho0, &done);
+      if (rc != PBCGS_SUCCESS) return rc;
+      if (done) {
+        if (folded) {
+          const int xg = (A->n + kWG - 1) / kWG;
+          if (fdv) k_fold_x<PC_VEC, false><<<xg, kWG, 0, ctx->stream>>>(A->n, x, fdv, ds);
+          else k_fold_x<PC_SCALAR, false><<<xg, kWG, 0, ctx->stream>>>(A->n, x, fdv, ds);
+          HIP_TRY(ctx, hipGetLastError());
+        }
+        info->value_codes = (A->kind == OP_CSR && uniform && A->n >= kViMinRows && pcl != PC_VEC) ? 1 : 0;
+        rc = with_op(A, [&](auto op) -> int { return true_relres(ctx, op, a, rho0, &info->relres_true); },
+                     compact_ok(o));
+        return rc != PBCGS_SUCCESS ? rc : info->status;
+      }
+    }
   }
 
   if (mp) {

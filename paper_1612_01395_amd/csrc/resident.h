@@ -1,0 +1,81 @@
+// Host interface of the resident solvers (resident.hpp): one cooperative
+// launch runs a whole binary64 solve with the Krylov vectors in registers and
+// LDS.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace pbcgs {
+
+struct DevState;
+
+constexpr int kResT = 512;          // threads per workgroup: 8 x wave64
+constexpr int kResMaxG = 256;       // workgroups: one per compute unit
+constexpr int kResMaxND = 7;        // diagonals
+constexpr int kResVecs = 5;         // global vectors a launch needs (three exchange buffers, x and r0)
+constexpr int kResWords = 2 * 2 * 5 * kResMaxG;  // tagged words of two reductions in flight
+constexpr size_t kResAux = 64;      // bytes of res_uniform's result: one value per diagonal, then a flag word
+constexpr size_t kResVecPad = 64;   // doubles a global vector holds beyond n
+
+// Operator: at most kResMaxND diagonals, offsets ascending, a mask of the
+// diagonals each row holds (a constant stencil derives its mask from the grid
+// extents), and either one value per diagonal (va == nullptr) or the values of
+// the diagonal layout.
+struct ResOp {
+  const uint32_t* mask;  // nullptr: a 5- or 7-point stencil on nx x ny x nz
+  const double* va;      // values va[d * ld + row], or nullptr: c[d]
+  int32_t n, nd, ld;
+  int32_t nx, ny, nz;
+  int32_t off[kResMaxND];
+  double c[kResMaxND];
+};
+
+struct ResJob {
+  int32_t variant, rr_period, rr_max, maxit, aform;
+  double tol;
+  bool pc;               // Jacobi applied as the algorithms write it
+  const double* dinv;    // its vector, or nullptr: the constant dinv_s
+  double dinv_s;
+  const double* b;
+  const double* x0;
+  double* hist;
+  double* vecs;          // kResVecs vectors of `stride` doubles, 16-byte aligned
+  int64_t stride;        // >= n + kResVecPad, even
+  unsigned long long* words;  // kResWords
+  int32_t* err;          // set to 1 when a wait timed out (nothing was written then)
+  DevState* st;          // the final state
+};
+
+struct ResPlan {
+  int K = 0;      // rows per thread; 0: the operator does not fit
+  int G = 0;      // workgroups
+  int H = 0;      // rows beyond the workgroup's own that its LDS windows hold, each side
+  bool far = false;  // the first and last diagonal are read from the exchange buffers
+};
+
+// The launch shape for an operator on a device with `cus` compute units, or
+// K = 0 where the resident form does not apply.
+ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus);
+
+// Whether the resident form implements a method (PBCGS_BICGSTAB ...).
+bool res_method(int32_t variant);
+
+// Writes to aux (kResAux device bytes) the value of each diagonal of the CSR
+// operator (rp, ci, va; op.mask its diagonals) and 0 after them when every row
+// holds that value, else 1.  plain: the stored values; else each times dinv of
+// its column (one rounding), or times ds when dinv is nullptr.
+hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, const double* va, const double* dinv,
+                       bool plain, double ds, void* aux, hipStream_t s);
+
+// x of the finished solve, inside job.vecs.
+inline double* res_x(const ResJob& j) { return j.vecs + 3 * j.stride; }
+
+hipError_t res_launch(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);
+
+// per method: its kernels live in a translation unit of their own
+hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);
+hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);
+hipError_t res_launch_cg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);
+
+}  // namespace pbcgs

@@ -1,0 +1,190 @@
+// Resident solves: the launch shape, the setup kernels and the dispatch per
+// method (the kernels themselves: resident_pipe.hip, resident_bicg.hip,
+// resident_cg.hip).
+#include <algorithm>
+#include <cstdint>
+#include <cstdlib>
+
+#include "../../include/pbcgs.h"
+#include "resident.hpp"
+
+namespace pbcgs {
+
+namespace {
+
+// Rows per thread that `op` can run with, and its windows: the diagonals other
+// than a far first and last one must lie within H rows, and two windows of
+// 512 K + 2 H doubles must fit the 160 KB of LDS beside the kernel's 2.6 KB.
+bool res_fit(const ResOp& op, int K, bool pc, int maxg, ResPlan* p) {
+  if (K > 8 && (pc || op.va != nullptr)) return false;
+  const int64_t rows = (int64_t)kResT * K;
+  const int64_t G = (op.n + rows - 1) / rows;
+  if (G > maxg) return false;
+  int64_t all = 0, inner = 0;
+  for (int d = 0; d < op.nd; ++d) {
+    const int64_t o = op.off[d] < 0 ? -(int64_t)op.off[d] : op.off[d];
+    all = std::max(all, o);
+    if (d > 0 && d < op.nd - 1) inner = std::max(inner, o);
+  }
+  // far diagonals cost two memory reads per row and product, a window's
+  // surroundings 2 H per workgroup: far once H would pass half its rows
+  const bool far = K > 8 || 2 * all > rows;
+  const int64_t H = ((far ? inner : all) + 1) & ~1ll;
+  if (K > 8 && G < 2) return false;
+  if ((int64_t)res_lds(K, 0) + 4 * H * 8 > 160 * 1024 - 4096) return false;
+  p->K = K;
+  p->G = (int)G;
+  p->H = (int)H;
+  p->far = far;
+  return true;
+}
+
+struct MethodCost {
+  int exchanges;   // per iteration
+  double per_row;  // microseconds per row of a thread
+};
+
+MethodCost method_cost(int32_t variant) {
+  switch (variant) {
+    case PBCGS_BICGSTAB: return {5, 0.5};
+    case PBCGS_CG: return {3, 0.23};
+    case PBCGS_CGCG: return {2, 0.33};
+    case PBCGS_PIPE_CG: return {1, 0.25};
+    default: return {2, 0.9};
+  }
+}
+
+}  // namespace
+
+ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus) {
+  ResPlan best;
+  if (op.nd < 1 || op.nd > kResMaxND || op.n < 1) return best;
+  const int maxg = std::min(cus, kResMaxG);
+  const char* e = std::getenv("PBCGS_RESIDENT_ROWS");
+  const int forced = e ? std::atoi(e) : 0;
+  double cost = 0.0;
+  const MethodCost m = method_cost(variant);
+  for (int K = 2; K <= 16; K *= 2) {
+    if (forced > 0 && K != forced) continue;
+    ResPlan p;
+    if (!res_fit(op, K, pc, maxg, &p)) continue;
+    // Microseconds of an iteration that depend on the shape, fitted to runs
+    // at 41^3, 64^3, 100^3 and 150^2: an exchange takes 0.015 us more per
+    // workgroup, a row per thread 0.23 us (CG) to 0.9 us (p-BiCGStab).  At 64^3
+    // p-BiCGStab takes 14.4 / 11.1 / 13.9 us with K = 2 / 4 / 8, BiCGStab
+    // 29.5 / 18.8 / 16.4, CG 16.5 / 10.7 / 9.0, p-CG 6.2 / 5.1 / 6.0.
+    const double c = m.exchanges * 0.015 * p.G + (pc ? 1.3 : 1.0) * m.per_row * K;
+    if (best.K == 0 || c < cost) {
+      best = p;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+// Clears the exchange words, the error word and the state's status (which a
+// finished solve overwrites).
+__global__ __launch_bounds__(256) void k_res_init(u64* words, int32_t* err, DevState* st) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < kResWords) words[i] = 0;
+  if (i == 0) {
+    *err = 0;
+    st->status = -1;
+  }
+}
+
+namespace {
+
+struct UniformArgs {
+  const uint32_t* mask;
+  const int32_t* rp;
+  const int32_t* ci;
+  const double* va;
+  const double* dinv;
+  double ds;
+  u64* ref;
+  int32_t* flag;
+  int32_t n, nd, plain;
+};
+
+__device__ __forceinline__ u64 uniform_bits(const UniformArgs& u, int32_t k) {
+  double v = u.va[k];
+  if (!u.plain) v = v * (u.dinv ? u.dinv[u.ci[k]] : u.ds);
+  return (u64)__double_as_longlong(v);
+}
+
+// Reference value of every diagonal: its first entry in the 8192 rows around
+// the middle (a diagonal with none there counts as varying).
+__global__ __launch_bounds__(1024) void k_uniform_ref(UniformArgs u) {
+  __shared__ int first[kResMaxND];
+  if (threadIdx.x < kResMaxND) first[threadIdx.x] = INT32_MAX;
+  __syncthreads();
+  const int32_t lo = max(u.n / 2 - 4096, 0), hi = min(u.n / 2 + 4096, u.n);
+  for (int32_t i = lo + (int32_t)threadIdx.x; i < hi; i += 1024) {
+    for (uint32_t m = u.mask[i]; m; m &= m - 1) {
+      const int d = __builtin_ctz(m);
+      if (first[d] > i) atomicMin(&first[d], i);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *u.flag = 0;
+  __syncthreads();
+  const int d = threadIdx.x;
+  if (d < u.nd) {
+    const int32_t i = first[d];
+    if (i == INT32_MAX) *u.flag = 1;
+    else u.ref[d] = uniform_bits(u, u.rp[i] + __builtin_popcount(u.mask[i] & ((1u << d) - 1u)));
+  }
+}
+
+// Every entry against its diagonal's reference.
+__global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) {
+  if (*u.flag) return;
+  u64 ref[kResMaxND];
+#pragma unroll
+  for (int d = 0; d < kResMaxND; ++d) ref[d] = d < u.nd ? u.ref[d] : 0;
+  bool same = true;
+  for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < u.n; i += gridDim.x * 256) {
+    const uint32_t m = u.mask[i];
+    int32_t k = u.rp[i];
+#pragma unroll
+    for (int d = 0; d < kResMaxND; ++d) {
+      if ((m >> d) & 1u) {
+        same = same && uniform_bits(u, k) == ref[d];
+        ++k;
+      }
+    }
+  }
+  if (!same) *u.flag = 1;
+}
+
+}  // namespace
+
+hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, const double* va, const double* dinv,
+                       bool plain, double ds, void* aux, hipStream_t s) {
+  u64* ref = static_cast<u64*>(aux);
+  const UniformArgs u = {op.mask, rp, ci, va, dinv, ds, ref, reinterpret_cast<int32_t*>(ref + kResMaxND), op.n, op.nd,
+                         plain ? 1 : 0};
+  k_uniform_ref<<<1, 1024, 0, s>>>(u);
+  k_uniform_check<<<std::min((op.n + 255) / 256, 2048), 256, 0, s>>>(u);
+  return hipGetLastError();
+}
+
+bool res_method(int32_t variant) { return variant != PBCGS_CA_BICGSTAB; }
+
+hipError_t res_launch(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
+  k_res_init<<<(kResWords + 255) / 256, 256, 0, s>>>(j.words, j.err, j.st);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  switch (j.variant) {
+    case PBCGS_PBICGSTAB:
+    case PBCGS_PBICGSTAB_RR: return res_launch_pipe(p, op, j, s);
+    case PBCGS_BICGSTAB: return res_launch_bicg(p, op, j, s);
+    case PBCGS_CG:
+    case PBCGS_CGCG:
+    case PBCGS_PIPE_CG: return res_launch_cg(p, op, j, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace pbcgs

@@ -1,0 +1,154 @@
+// Resident BiCGStab (Algorithms 7 and 10): see resident.hpp.
+#include <type_traits>
+
+#include "resident.hpp"
+
+namespace pbcgs {
+
+namespace {
+
+// Five exchanges per iteration, two of them barriers only (q^ and p^ have to
+// reach the other workgroups before their products).  Per row in registers:
+// r0, r, s, y and x, with Jacobi also p and q.  Window 0 holds p^ (p), window
+// 1 q^ (q).
+template <int K, int ND, bool FAR, bool UNI, bool PC>
+__global__ __launch_bounds__(kResT) void k_res_bicg(ResOpT<ND> op, ResArgs a) {
+  using R = Res<K, ND, FAR, UNI, PC>;
+  constexpr int KP = R::KP;
+  extern __shared__ __align__(16) double sm[];
+  __shared__ typename R::Shared sh;
+  R g(op, a, sh, sm);
+  constexpr int P = 0, Q = 1;
+
+  D2 r0[KP], r[KP], s[KP], y[KP];
+  D2 p[PC ? KP : 1], q[PC ? KP : 1];
+  typename R::X x;
+  State st = g.start();
+
+  // r_0 = p_0 = b - A x_0
+  g.load_x0(x, Q);
+  if (!g.barrier()) return;
+  g.halo(Q);
+  double g0[1];
+  {
+    typename R::template Tree<1> tr(sh);
+    g.product(Q, [&](auto jc, D2 ax) {
+      constexpr int j = decltype(jc)::value;
+      const D2 v = g.get(a.b, j) - ax;
+      r0[j] = v;
+      r[j] = v;
+      if constexpr (PC) {
+        p[j] = v;
+        g.put(P, j, g.precond(j, v));
+      } else {
+        g.put(P, j, v);
+      }
+      double d[1] = {v.x * v.x + v.y * v.y};
+      tr.template add<j>(d);
+    });
+    if (!g.template exchange<1>(tr.top, g0)) return;
+  }
+  fin_setup_gamma(st, a.hist, g0[0]);
+  uniform(st);
+  for (int64_t i = 0; st.status == DS_RUNNING && i < a.maxit; ++i) {
+    {  // s = A p^ ; alpha
+      g.halo(P);
+      typename R::template Tree<1> tr(sh);
+      g.product(P, [&](auto jc, D2 v) {
+        constexpr int j = decltype(jc)::value;
+        s[j] = v;
+        double d[1] = {r0[j].x * v.x + r0[j].y * v.y};
+        tr.template add<j>(d);
+      });
+      double g1[1];
+      if (!g.template exchange<1>(tr.top, g1)) return;
+      fin_bicg_alpha(st, g1[0]);
+      uniform(st);
+      if (st.status != DS_RUNNING) break;
+    }
+    const double alpha = st.alpha;
+    double g2[2];
+    {  // q = r - alpha s ; y = A q^ ; omega
+      g.next(Q);
+#pragma unroll
+      for (int j = 0; j < KP; ++j) {
+        const D2 v = r[j] - alpha * s[j];
+        if constexpr (PC) {
+          q[j] = v;
+          g.put(Q, j, g.precond(j, v));
+        } else {
+          g.put(Q, j, v);
+        }
+      }
+      if (!g.barrier()) return;
+      g.halo(Q);
+      typename R::template Tree<2> tr(sh);
+      g.product(Q, [&](auto jc, D2 v) {
+        constexpr int j = decltype(jc)::value;
+        D2 qj;
+        if constexpr (PC) qj = q[j];
+        else qj = g.own(Q, j);
+        y[j] = v;
+        double d[2] = {qj.x * v.x + qj.y * v.y, v.x * v.x + v.y * v.y};
+        tr.template add<j>(d);
+      });
+      if (!g.template exchange<2>(tr.top, g2)) return;
+    }
+    const bool yz = uniform((int32_t)fin_omega(st, a.hist, g2[0], g2[1])) != 0;
+    uniform(st);
+    if (yz) {
+#pragma unroll
+      for (int j = 0; j < KP; ++j) g.set_x(x, j, g.get_x(x, j) + alpha * g.own(P, j));
+      break;
+    }
+    if (st.status != DS_RUNNING) break;
+    const double omega = st.omega;
+    {  // x, r ; stop test, beta
+      typename R::template Tree<2> tr(sh);
+      each_pair<KP>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const D2 qh = g.own(Q, j);
+        D2 qj;
+        if constexpr (PC) qj = q[j];
+        else qj = qh;
+        g.set_x(x, j, g.get_x(x, j) + alpha * g.own(P, j) + omega * qh);
+        r[j] = qj - omega * y[j];
+        double d[2] = {r0[j].x * r[j].x + r0[j].y * r[j].y, r[j].x * r[j].x + r[j].y * r[j].y};
+        tr.template add<j>(d);
+      });
+      if (!g.template exchange<2>(tr.top, g2)) return;
+    }
+    fin_bicg_beta(st, a.hist, g2[0], g2[1]);
+    uniform(st);
+    if (st.status != DS_RUNNING) break;
+    const double beta = st.beta;
+    g.next(P);
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+      D2 po;
+      if constexpr (PC) po = p[j];
+      else po = g.own(P, j);
+      const D2 pn = r[j] + beta * (po - omega * s[j]);
+      if constexpr (PC) {
+        p[j] = pn;
+        g.put(P, j, g.precond(j, pn));
+      } else {
+        g.put(P, j, pn);
+      }
+    }
+    if (!g.barrier()) return;
+  }
+  g.finish(x, st);
+}
+
+}  // namespace
+
+hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
+  return res_dispatch(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
+    constexpr int K = decltype(k)::value, ND = decltype(nd)::value;
+    return res_go<ND>(&k_res_bicg<K, ND, decltype(far)::value, decltype(uni)::value, decltype(pc)::value>, K, p, op, j,
+                      s);
+  });
+}
+
+}  // namespace pbcgs
