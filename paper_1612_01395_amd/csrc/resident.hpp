@@ -323,74 +323,67 @@ struct Res {
     __syncthreads();
   }
 
-  // y = A v for pairs c0 .. c0 + CJ - 1, v in window w.  Each row sums its
-  // present diagonals in ascending order from 0.0.
-  // `pre` runs between the issue of the far loads and the arithmetic.
-  template <class P>
-  __device__ __forceinline__ void spmv(int w, int c0, D2 (&y)[CJ], P&& pre) const {
-    D2 f0[CJ], f1[CJ];
-    const int32_t rowc = fresh(row0) + 128 * c0;
-    const double* const pc = win(w) + (fresh(li0) + 128 * c0);
-    if constexpr (FAR) {
-      const auto r = rsrc(w);
-#pragma unroll
-      for (int j = 0; j < CJ; ++j) {
-        f0[j] = load2(r, rowc + 128 * j + op.off[0]);
-        f1[j] = load2(r, rowc + 128 * j + op.off[ND - 1]);
-      }
-    }
-    pre();
-#pragma unroll
-    for (int j = 0; j < CJ; ++j) {
-      const double* p = pc + 128 * j;
-      __builtin_amdgcn_sched_barrier(0);
-      D2 xs[ND];
-#pragma unroll
-      for (int d = 0; d < ND; ++d) {
-        if (FAR && d == 0) xs[d] = f0[j];
-        else if (FAR && d == ND - 1) xs[d] = f1[j];
-        else xs[d] = *reinterpret_cast<const D2u*>(p + op.off[d]);
-      }
-      D2 vs[ND];
-      if constexpr (!UNI) {
-        const int32_t rv = min(rowc + 128 * j, (n - 1) & ~1);
-#pragma unroll
-        for (int d = 0; d < ND; ++d) vs[d] = *reinterpret_cast<const D2*>(&op.va[(int64_t)op.vd[d] * op.ld + rv]);
-      }
-      const int jj = c0 + j;
-      const uint32_t m = fresh(mk[jj / 2]) >> (16 * (jj % 2)), u = fresh_uniform(all[jj / 4]) >> (8 * (jj % 4));
-      D2 acc = {0.0, 0.0};
-#pragma unroll
-      for (int d = 0; d < ND; ++d) {
-        const double v0 = UNI ? op.c[d] : vs[d].x, v1 = UNI ? op.c[d] : vs[d].y;
-        const double t0 = acc.x + v0 * xs[d].x, t1 = acc.y + v1 * xs[d].y;
-        if ((u >> d) & 1u) {
-          acc.x = t0;
-          acc.y = t1;
-        } else {
-          acc.x = ((m >> d) & 1u) ? t0 : acc.x;
-          acc.y = ((m >> (8 + d)) & 1u) ? t1 : acc.y;
-        }
-      }
-      y[j] = acc;
-    }
-  }
-
   // y = A v for every pair, v in window w, handed to f(j, y_j) with j a
-  // compile-time constant.  load(j) is called for the same pairs before their
-  // arithmetic, to issue loads f(j) needs.
+  // compile-time constant; load(j) is called before pair j's arithmetic, to
+  // issue loads f(j) needs.  Each row sums its present diagonals in ascending
+  // order from 0.0.  The far diagonals' loads go out CJ pairs at a time; the
+  // pairs themselves are kept apart (one pair's temporaries at a time is what
+  // the registers hold beside the vectors).
   template <class L, class F>
   __device__ __forceinline__ void product(int w, L&& load, F&& f) const {
     each_pair<KP / CJ>([&](auto c) {
       constexpr int c0 = decltype(c)::value * CJ;
-      D2 y[CJ];
-      spmv(w, c0, y, [&]() {
-        each_pair<CJ>([&](auto jj) { load(std::integral_constant<int, c0 + decltype(jj)::value>()); });
-      });
-      each_pair<CJ>([&](auto jj) {
-        constexpr int j = decltype(jj)::value;
+      const int32_t rowc = fresh(row0) + 128 * c0;
+      const double* const pc = win(w) + (fresh(li0) + 128 * c0);
+      D2 f0[CJ], f1[CJ];
+      if constexpr (FAR) {
+        const auto r = rsrc(w);
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) {
+          f0[j] = load2(r, rowc + 128 * j + op.off[0]);
+          f1[j] = load2(r, rowc + 128 * j + op.off[ND - 1]);
+        }
+      }
+      each_pair<CJ>([&](auto jc) {
+        constexpr int j = decltype(jc)::value, jj = c0 + j;
         __builtin_amdgcn_sched_barrier(0);
-        f(std::integral_constant<int, c0 + j>(), y[j]);
+        load(std::integral_constant<int, jj>());
+        const double* p = pc + 128 * j;
+        D2 xs[ND], vs[ND];
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+          if (FAR && d == 0) xs[d] = f0[j];
+          else if (FAR && d == ND - 1) xs[d] = f1[j];
+          else xs[d] = *reinterpret_cast<const D2u*>(p + op.off[d]);
+        }
+        if constexpr (!UNI) {
+          const int32_t rv = min(rowc + 128 * j, (n - 1) & ~1);
+#pragma unroll
+          for (int d = 0; d < ND; ++d) vs[d] = *reinterpret_cast<const D2*>(&op.va[(int64_t)op.vd[d] * op.ld + rv]);
+        }
+        const uint32_t m = fresh(mk[jj / 2]) >> (16 * (jj % 2)), u = fresh_uniform(all[jj / 4]) >> (8 * (jj % 4));
+        // Two forms: every row of the block holds all but the slots beside the
+        // middle one (a grid's x neighbours, which the ends of a line miss), or
+        // any slot may be missing.
+        D2 acc = {0.0, 0.0};
+        auto sum = [&](uint32_t test) {
+#pragma unroll
+          for (int d = 0; d < ND; ++d) {
+            const double v0 = UNI ? op.c[d] : vs[d].x, v1 = UNI ? op.c[d] : vs[d].y;
+            const double t0 = acc.x + v0 * xs[d].x, t1 = acc.y + v1 * xs[d].y;
+            if ((test >> d) & 1u) {
+              acc.x = ((m >> d) & 1u) ? t0 : acc.x;
+              acc.y = ((m >> (8 + d)) & 1u) ? t1 : acc.y;
+            } else {
+              acc.x = t0;
+              acc.y = t1;
+            }
+          }
+        };
+        constexpr uint32_t full = (1u << ND) - 1u, ends = 5u << (ND / 2 - 1);
+        if (((u | ends) & full) == full) sum(ends);
+        else sum(full);
+        f(std::integral_constant<int, jj>(), acc);
       });
     });
   }

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kResT) void k_res_pipe(ResOpT<ND> op, ResArgs a) {
     {
       const double omega = st.omega;
       typename R::template Tree<2> tr(sh);
-      if (res_rr_due(a, i - 1)) {
+      if (__builtin_expect(uniform((int32_t)res_rr_due(a, i - 1)) != 0, 0)) {
         // after a replacement: p^, then s = A p^ and z = A s^ from their definitions
         g.next(Z);
 #pragma unroll
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kResT) void k_res_pipe(ResOpT<ND> op, ResArgs a) {
     if (st.status != DS_RUNNING) break;
     const double omega = st.omega;
     typename R::template Tree<5> tr(sh);
-    if (res_rr_due(a, i)) {
+    if (__builtin_expect(uniform((int32_t)res_rr_due(a, i)) != 0, 0)) {
       // x, then r = b - A x, r^, w = A r^, w^ from their definitions
       g.next(W);
 #pragma unroll
