@@ -716,11 +716,13 @@ struct DiaViOpT {
   int32_t n;
   int32_t nd;
   int32_t ld;
-  int32_t pad_ = 0;
+  uint32_t one;   // bit d: diagonal d holds the one value c[d], and its table is not read
   int32_t off[kViDia];
+  V c[kViDia];
 
-  __device__ __forceinline__ V val(int d, uint32_t c, bool present) const {
-    const uint64_t b = tab[d * kViTab + (present ? c : 0u)];
+  __device__ __forceinline__ V val(int d, uint32_t k, bool present) const {
+    if ((one >> d) & 1u) return c[d];  // uniform: a scalar operand instead of a gather per row
+    const uint64_t b = tab[d * kViTab + (present ? k : 0u)];
     if constexpr (sizeof(V) == 8) return __longlong_as_double((long long)b);
     else return __uint_as_float((uint32_t)b);
   }
@@ -1154,6 +1156,30 @@ __device__ __forceinline__ void gather_sums(const Args& a, double (&res)[ND]) {
   wg_sum_all<ND, T>(v, tot);
 #pragma unroll
   for (int k = 0; k < ND; ++k) res[k] = double(tot[k] + T(0));
+}
+
+// Folds G partial sums of each of gridDim.y sums (strides `stride`) to one per
+// kFold of them, each the balanced tree over its kFold (zeros past G), in the
+// arithmetic type T of the sums.
+constexpr int kFold = kMaxG;
+template <class T>
+__global__ __launch_bounds__(kWG) void k_fold_sums(const double* __restrict__ in, double* __restrict__ out, int32_t G,
+                                                   int32_t stride) {
+  __shared__ T w[4];
+  const int64_t row = (int64_t)blockIdx.y * stride;
+  const int base = (int)blockIdx.x * kFold + (int)threadIdx.x * kChunk;
+  T c[kChunk];
+#pragma unroll
+  for (int j = 0; j < kChunk; ++j) {
+    const T p = T(in[row + min(base + j, G - 1)]);
+    c[j] = base + j < G ? p : T(0);
+  }
+  T v[1] = {(c[0] + c[1]) + (c[2] + c[3])};
+  static_assert(kChunk == 4, "four partials per thread");
+  wave_sum63<1, T>(v);
+  if ((threadIdx.x & 63) == 63) w[threadIdx.x >> 6] = v[0];
+  __syncthreads();
+  if (threadIdx.x == 0) out[row + blockIdx.x] = double((w[0] + w[1]) + (w[2] + w[3]));
 }
 
 // Index of this workgroup among the workgroups of its system.  With

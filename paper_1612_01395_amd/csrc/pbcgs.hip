@@ -95,6 +95,8 @@ struct pbcgs_ctx_s {
   DevState* hst = nullptr;  // pinned host copies: slots 0, 1 for polling, 2 for reads of a state or a scalar
   int32_t* flag = nullptr;  // structural error flags of utility kernels
   int coop = -1;            // device supports cooperative launches (-1: not asked yet)
+  double* bigpart = nullptr;     // partial sums of launches of more than kMaxG workgroups
+  size_t bigpart_cap = 0;        // doubles
   unsigned char* res = nullptr;  // resident solves: exchange words, then kResAux bytes
   int32_t* hflag = nullptr; // pinned host copy
   double* part = nullptr;   // PB_COUNT buffers of kMaxD * kMaxG partial sums
@@ -559,6 +561,8 @@ int true_relres(pbcgs_ctx_t ctx, const Op& op, const Args& a0, double rho0, doub
 // ---------------------------------------------------------------------------
 // Per-(operator, preconditioner) driver.
 // ---------------------------------------------------------------------------
+constexpr int32_t kManyRows = 1 << 21;  // see Driver::take_many
+constexpr int kManyR = 8;
 // MP: precision form (Op is the binary32 operator, Op64 the binary64 one).
 template <class Op, int PC, class Op64 = Op, bool MP = false>
 struct Driver {
@@ -570,6 +574,8 @@ struct Driver {
   bool timing = false;
   bool true_res = true;  // false: the caller computes relres_true itself
   double rho0 = 0.0;     // ||r_0|| of the finished solve
+  int32_t many_R = 0, many_G = 0;  // the shape of take_many()
+  bool finishing = false;          // inside finish(): the pending reduction is consumed
   int64_t q = 0;  // kernel launches of this solve that passed the state on
   std::vector<std::pair<hipEvent_t, hipEvent_t>> tev[2];
   size_t ev_used = 0;
@@ -609,20 +615,80 @@ struct Driver {
   }
 
   // Arguments of the next launch: state slots by launch parity, partials.
+  // With many workgroups (see take_many) the partial sums a kernel consumes are
+  // first folded to one per kFold of them.
   Args L(int pin, int pout, bool first = false, int mode = 0) {
     Args b = a;
     b.mode = mode;
     b.sin = ctx->st + (q & 1);
     b.sout = ctx->st + ((q + 1) & 1);
-    b.pin = pin >= 0 ? part_buf(ctx, pin) : nullptr;
-    b.pout = pout >= 0 ? part_buf(ctx, pout) : nullptr;
-    b.Gin = a.G;
     b.first = first ? 1 : 0;
+    if (many_G > 0) {
+      b.G = many_G;
+      b.R = many_R;
+      b.pstride = many_G;
+      const size_t buf = (size_t)kMaxD * many_G;  // raw sums of every role, then the folded ones
+      const int nb = (many_G + kFold - 1) / kFold;
+      b.pout = pout >= 0 ? ctx->bigpart + pout * buf : nullptr;
+      b.pin = nullptr;
+      b.Gin = nb;
+      // BiCGStab names the setup's sums in every iteration and reads them in the first
+      if (pin >= 0 && !(pin == PB_SETUP1 && o.variant == PBCGS_BICGSTAB && !first && !finishing)) {
+        const double* raw = ctx->bigpart + pin * buf;
+        double* folded = ctx->bigpart + (PB_COUNT + pin) * buf;
+        k_fold_sums<std::conditional_t<MP, float, double>>
+            <<<dim3((unsigned)nb, kMaxD), kWG, 0, ctx->stream>>>(raw, folded, many_G, many_G);
+        b.pin = folded;
+      }
+    } else {
+      b.pin = pin >= 0 ? part_buf(ctx, pin) : nullptr;
+      b.pout = pout >= 0 ? part_buf(ctx, pout) : nullptr;
+      b.Gin = a.G;
+    }
     ++q;
     return b;
   }
 
-  dim3 grid() const { return dim3((unsigned)a.G); }
+  // Many small workgroups instead of at most 1,024 large ones, for systems of
+  // more than kManyRows rows.  With 1,024 workgroups every wave sweeps
+  // thousands of rows of its own and all sweep at once, so a row's neighbours
+  // a line or a plane away come round after more bytes than the caches hold
+  // and the gathered vector is fetched several times; small workgroups,
+  // dispatched in order, sweep the system as one window.  Each kernel's sums
+  // are folded by one small kernel before they are consumed.
+  bool take_many() {
+    const int mode = env_int("PBCGS_MANY", -1);
+    if (mode == 0 || ctx->noalloc || (mode < 0 && a.n <= kManyRows)) return false;
+    if (std::getenv("PBCGS_R") || std::getenv("PBCGS_GTARGET")) return false;
+    const int R = mode > 0 ? mode : kManyR;
+    const int64_t G = ((int64_t)a.n + 256 * (int64_t)R - 1) / (256 * (int64_t)R);
+    if (G <= kMaxG || G > (int64_t)kMaxG * kFold) return false;
+    const size_t need = 2 * (size_t)PB_COUNT * kMaxD * (size_t)G;
+    if (ctx->bigpart_cap < need) {
+      if (ctx->bigpart) {
+        (void)hipStreamSynchronize(ctx->stream);
+        (void)hipFree(ctx->bigpart);
+        ctx->bigpart_cap = 0;
+        for (auto& g : ctx->graphs) (void)hipGraphExecDestroy(g.second);
+        ctx->graphs.clear();
+      }
+      if (hipMalloc((void**)&ctx->bigpart, need * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->bigpart = nullptr;
+        return false;
+      }
+      ctx->bigpart_cap = need;
+    }
+    poison(ctx, ctx->bigpart, need * sizeof(double));
+    many_R = R;
+    many_G = (int32_t)G;
+    a.wg = -1;  // in dispatch order
+    return true;
+  }
+  int32_t shape_R() const { return many_G > 0 ? many_R : a.R; }
+  int32_t shape_G() const { return many_G > 0 ? many_G : a.G; }
+
+  dim3 grid() const { return dim3((unsigned)shape_G()); }
 
   // the unpreconditioned binary64 BiCGStab kernels likewise, and the p-BiCGStab
   // ones on the diagonal layout and on a stencil with an even x extent, whose
@@ -638,7 +704,7 @@ struct Driver {
           return false;
         }
       }
-      return a.R >= 2 && env_int("PBCGS_TWO_ROWS64", 1) != 0;
+      return shape_R() >= 2 && env_int("PBCGS_TWO_ROWS64", 1) != 0;
     }
     return false;
   }
@@ -653,7 +719,7 @@ struct Driver {
       } else if constexpr (!IsDia<Op>::value) {
         return false;
       }
-      return a.R >= 2 && env_int("PBCGS_TWO_ROWS64", 1) != 0;
+      return shape_R() >= 2 && env_int("PBCGS_TWO_ROWS64", 1) != 0;
     }
     return false;
   }
@@ -661,14 +727,14 @@ struct Driver {
   // the binary32 kernels take two rows per lane when the operator supports it
   // and every wave owns at least two 64-row blocks (PBCGS_TWO_ROWS=0 turns it off)
   bool two_rows() const {
-    if constexpr (MP && HasSpmv2<Op>::value) return a.R >= 2 && env_int("PBCGS_TWO_ROWS", 1) != 0;
+    if constexpr (MP && HasSpmv2<Op>::value) return shape_R() >= 2 && env_int("PBCGS_TWO_ROWS", 1) != 0;
     return false;
   }
   // the binary32 fused kernels take four rows per lane (16-byte vector
   // accesses) when the operator supports it and every wave owns at least four
   // 64-row blocks (PBCGS_FOUR_ROWS=0 turns it off; then two rows per lane)
   bool four_rows() const {
-    if constexpr (MP && HasSpmv4<Op>::value) return a.R >= 4 && env_int("PBCGS_FOUR_ROWS", 1) != 0;
+    if constexpr (MP && HasSpmv4<Op>::value) return shape_R() >= 4 && env_int("PBCGS_FOUR_ROWS", 1) != 0;
     return false;
   }
   // the replacement steps of the binary32 form with two rows per lane too
@@ -892,6 +958,7 @@ struct Driver {
   // The reduction left pending by the last kernel, finished by one workgroup.
   void finish(int64_t iters_launched) {
     hipStream_t s = ctx->stream;
+    finishing = true;
     if constexpr (MP) {
       if (iters_launched == 0) k_mp_finish<1><<<1, kWG, 0, s>>>(L(PB_SETUP2, -1));
       else k_mp_finish<0><<<1, kWG, 0, s>>>(L(PB_B, -1, false, was_forced(iters_launched - 1) ? 1 : 0));
@@ -931,7 +998,7 @@ struct Driver {
     k.append(reinterpret_cast<const char*>(&op), sizeof(Op));
     k.append(reinterpret_cast<const char*>(&op64), sizeof(Op64));
     // the kernel forms the environment selects are part of the schedule
-    std::snprintf(buf, sizeof buf, "|%d|%d|%d|%d|%lld|%d|%d|%d%d%d%d|", PC, MP ? 1 : 0, o.variant, m,
+    std::snprintf(buf, sizeof buf, "|%d|%d|%d|%d|%d|%d|%lld|%d|%d|%d%d%d%d|", many_R, many_G, PC, MP ? 1 : 0, o.variant, m,
                   (long long)(q & 1), i0 == 0 ? 1 : 0, (int)(i0 & 1), four_rows() ? 1 : 0, two_rows() ? 1 : 0,
                   two_rows64() ? 1 : 0, cg_two_rows() ? 1 : 0);
     k += buf;
@@ -986,6 +1053,7 @@ struct Driver {
     HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
     k_init_state<<<1, 64, 0, s>>>(ctx->st, o.tol);
     q = 0;
+    take_many();
     setup();
     HIP_TRY(ctx, hipGetLastError());
     // Chunks of at most `check` iterations; the status after chunk c is polled
@@ -1055,6 +1123,7 @@ struct Driver {
           k_mp_rr_r<Op64><<<grid(), kWG, 0, s>>>(op64, L(-1, -1));
           launch_rr_w();
           HIP_TRY(ctx, hipGetLastError());
+          finishing = false;
           forced.push_back((int64_t)fin.iters - 1);
           launched = fin.iters;
           last_it = fin.iters;  // predict the remaining iterations from the true residual
@@ -1086,8 +1155,8 @@ struct Driver {
     info->syncs_per_iter = syncs_per_iteration(o.variant);
     info->relres_rec = fin.relres;
     info->ms = ms;
-    info->rows_per_wave_blocks = a.R;
-    info->workgroups = a.G;
+    info->rows_per_wave_blocks = shape_R();
+    info->workgroups = shape_G();
     for (int k = 0; k < 2; ++k) {
       double tot = 0.0;
       for (auto& pr : tev[k]) {
@@ -1722,6 +1791,7 @@ int pbcgs_ctx_destroy(pbcgs_ctx_t ctx) {
   if (ctx->part) (void)hipFree(ctx->part);
   if (ctx->flag) (void)hipFree(ctx->flag);
   if (ctx->res) (void)hipFree(ctx->res);
+  if (ctx->bigpart) (void)hipFree(ctx->bigpart);
   if (ctx->st) (void)hipFree(ctx->st);
   if (ctx->hst) (void)hipHostFree(ctx->hst);
   if (ctx->hflag) (void)hipHostFree(ctx->hflag);
@@ -1979,14 +2049,14 @@ static bool vi_operator(pbcgs_ctx_t ctx, const DiaOpT<V>& d, DiaViOpT<V>* out, i
   uint64_t* tab = reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->vi[slot]) + code_bytes);
   k_vi_reset<<<(d.nd * kViTab + 1 + kWG - 1) / kWG, kWG, 0, ctx->stream>>>(tab, d.nd);
   k_vi_collect<<<std::min((d.n + kWG - 1) / kWG, 1024), kWG, 0, ctx->stream>>>(d, tab);
-  uint64_t overflow = 1;
-  if (hipMemcpyAsync(&overflow, tab + (size_t)d.nd * kViTab, sizeof overflow, hipMemcpyDeviceToHost, ctx->stream) !=
-          hipSuccess ||
+  uint64_t h[kViDia * kViTab + 1];  // the tables, then the overflow word
+  const size_t words = (size_t)d.nd * kViTab + 1;
+  if (hipMemcpyAsync(h, tab, words * sizeof(uint64_t), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
       hipStreamSynchronize(ctx->stream) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  if (overflow != 0) return false;
+  if (h[words - 1] != 0) return false;
   k_vi_encode<<<(d.ld + kWG - 1) / kWG, kWG, 0, ctx->stream>>>(d, tab, code);
   DiaViOpT<V> v;
   std::memset(&v, 0, sizeof v);
@@ -1995,7 +2065,20 @@ static bool vi_operator(pbcgs_ctx_t ctx, const DiaOpT<V>& d, DiaViOpT<V>* out, i
   v.n = d.n;
   v.nd = d.nd;
   v.ld = d.ld;
-  for (int k = 0; k < d.nd; ++k) v.off[k] = d.off[k];
+  for (int k = 0; k < d.nd; ++k) {
+    v.off[k] = d.off[k];
+    int found = 0;
+    uint64_t bits = 0;
+    for (int t = 0; t < kViTab; ++t) {
+      if (h[k * kViTab + t] == kViEmpty) continue;
+      ++found;
+      bits = h[k * kViTab + t];
+    }
+    if (found == 1) {
+      v.one |= 1u << k;
+      std::memcpy(&v.c[k], &bits, sizeof(V));  // binary32 patterns are the low half
+    }
+  }
   *out = v;
   return true;
 }
