@@ -909,97 +909,120 @@ struct Conv27Op {
     constexpr int blo = dy > 0 ? 1 : 0, bhi = dy < 0 ? 0 : 1;
     constexpr int clo = dz > 0 ? 1 : 0, chi = dz < 0 ? 0 : 1;
     constexpr int cnt = (ahi - alo + 1) * (bhi - blo + 1) * (chi - clo + 1);
-    double ks = 0.0;
+    // the assembly's 0.0 + K differs from K for K = -0.0 only, by the sign of a
+    // zero coupling, which no sum of the row can show
+    double ks = K[clo][blo][alo];
 #pragma unroll
     for (int c = clo; c <= chi; ++c)
 #pragma unroll
       for (int b = blo; b <= bhi; ++b)
 #pragma unroll
-        for (int a = alo; a <= ahi; ++a) ks = ks + K[c][b][a];
+        for (int a = alo; a <= ahi; ++a)
+          if (c != clo || b != blo || a != alo) ks = ks + K[c][b][a];
     return ks * (1.0 / (double)cnt);
   }
 
+  // Sum of the 26 kbar.
   template <int E>
-  static __device__ __forceinline__ void kbars(const double (&K)[2][2][2], double (&kb)[27], double& dsum) {
+  static __device__ __forceinline__ void kbars(const double (&K)[2][2][2], double& dsum) {
     if constexpr (E < 27) {
-      if constexpr (E != 13) {
-        kb[E] = kbar<E>(K);
-        dsum = dsum + kb[E];
-      }
-      kbars<E + 1>(K, kb, dsum);
+      if constexpr (E != 13) dsum = dsum + kbar<E>(K);
+      kbars<E + 1>(K, dsum);
     }
   }
 
   // Entry E = (dz+1)*9 + (dy+1)*3 + (dx+1) of the row (before any scaling).
   template <int E>
-  __device__ __forceinline__ double entry(const double (&kb)[27], double diag) const {
+  __device__ __forceinline__ double entry(const double (&K)[2][2][2], double diag) const {
     if constexpr (E == 13) {
       return diag;
     } else {
       constexpr int dx = E % 3 - 1, dy = (E / 3) % 3 - 1, dz = E / 9 - 1;
-      double a = -kb[E];
+      const double kb = kbar<E>(K);
+      double a = -kb;
       if constexpr ((dx != 0) + (dy != 0) + (dz != 0) == 1) {
         constexpr int ax = dx != 0 ? 0 : (dy != 0 ? 1 : 2);
         constexpr int side = dx != 0 ? dx : (dy != 0 ? dy : dz);
         const bool upwind = ((upneg >> ax) & 1) ? (side < 0) : (side > 0);
-        if (upwind) a = -kb[E] - hab[ax];
+        if (upwind) a = -kb - hab[ax];
       }
       return a;
     }
   }
 
-  // The three terms of grid line L = (dz+1)*3 + (dy+1) (dx = -1, 0, +1).  All
-  // 64 lanes take part: the centre value x[row + off] is loaded by every lane
-  // (its own row when the line leaves the grid, a value then never used), and
-  // the dx = -1 / +1 neighbours come from the adjacent lanes by a wave shift;
-  // lanes 0 and 63 receive instead the one extra value loaded per line (the
-  // element before / after the block), supplied as the shift's fill value.
-  // Terms whose neighbour lies outside the grid are not added (the selected
-  // accumulator keeps its value), as the assembled row has no such entry.
-  template <int L, class X>
-  __device__ __forceinline__ void line(int32_t row, int32_t b0, int lane, int32_t i, int32_t j, int32_t k,
-                                       const double (&kb)[27], double diag, const X* __restrict__ x, V& acc) const {
-    if constexpr (L < 9) {
-      constexpr int dy = L % 3 - 1, dz = L / 3 - 1;
-      const int32_t N = n * n * n;
-      const int32_t off = n * dy + n * n * dz;
-      const bool lin = (dy < 0 ? j > 0 : (dy > 0 ? j < n - 1 : true)) && (dz < 0 ? k > 0 : (dz > 0 ? k < n - 1 : true));
-      const int32_t c = lin ? row + off : row;
-      const int32_t e = min(max(lane < 32 ? b0 + off - 1 : b0 + 64 + off, 0), N - 1);
-      const X xc = x[c], xe = x[e];
-      const X xs[3] = {wave_shift<kWaveShr1>(xe, xc), xc, wave_shift<kWaveShl1>(xe, xc)};
-      double ss[3] = {1.0, 1.0, 1.0};
-      if constexpr (FOLD) {
-        const double sc = dscale[c], se = dscale[e];
-        ss[0] = wave_shift<kWaveShr1>(se, sc);
-        ss[1] = sc;
-        ss[2] = wave_shift<kWaveShl1>(se, sc);
-      }
+  // What the three grid lines of plane dz = P - 1 (dy = -1, 0, +1) are read
+  // for: every lane's centre value x[row + off] (its own row when the line
+  // leaves the grid, a value then never used), and one extra value per half
+  // wave, the element before / after the block, which lanes 0 and 63 need.
+  template <class X>
+  struct Plane {
+    X xc[3], xe[3];
+    double sc[3], se[3];
+    bool lin[3];
+  };
+  template <int P, class X>
+  __device__ __forceinline__ void load_plane(int32_t row, int32_t b0, int lane, int32_t j, int32_t k,
+                                             const X* __restrict__ x, Plane<X>& q) const {
+    constexpr int dz = P - 1;
+    const int32_t N = n * n * n;
+    const bool in_z = dz < 0 ? k > 0 : (dz > 0 ? k < n - 1 : true);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const bool in = lin && (q == 0 ? i > 0 : (q == 2 ? i < n - 1 : true));
-        double a = (q == 0) ? entry<L * 3>(kb, diag) : (q == 1 ? entry<L * 3 + 1>(kb, diag) : entry<L * 3 + 2>(kb, diag));
-        if constexpr (FOLD) a = a * ss[q];
-        const V t = acc + V(a) * V(xs[q]);
-        acc = in ? t : acc;
+    for (int l = 0; l < 3; ++l) {
+      const int dy = l - 1;
+      const int32_t off = n * dy + n * n * dz;
+      q.lin[l] = in_z && (dy < 0 ? j > 0 : (dy > 0 ? j < n - 1 : true));
+      const int32_t c = q.lin[l] ? row + off : row;
+      const int32_t e = min(max(lane < 32 ? b0 + off - 1 : b0 + 64 + off, 0), N - 1);
+      q.xc[l] = x[c];
+      q.xe[l] = x[e];
+      if constexpr (FOLD) {
+        q.sc[l] = dscale[c];
+        q.se[l] = dscale[e];
       }
-      line<L + 1>(row, b0, lane, i, j, k, kb, diag, x, acc);
     }
   }
 
-  __device__ __forceinline__ double diag_of(const double (&kb)[27], double dsum) const {
-    (void)kb;
+  // The nine terms of plane dz = P - 1 in ascending column order.  The dx = -1
+  // / +1 neighbours come from the adjacent lanes by a wave shift; lanes 0 and
+  // 63 receive the extra value as the shift's fill.  Terms whose neighbour
+  // lies outside the grid are not added (the selected accumulator keeps its
+  // value), as the assembled row has no such entry.
+  template <int P, int L, class X>
+  __device__ __forceinline__ void plane_terms(int32_t i, const double (&K)[2][2][2], double diag, const Plane<X>& q,
+                                              V& acc) const {
+    if constexpr (L < 3) {
+      constexpr int E = P * 9 + L * 3;
+      const X xs[3] = {wave_shift<kWaveShr1>(q.xe[L], q.xc[L]), q.xc[L], wave_shift<kWaveShl1>(q.xe[L], q.xc[L])};
+      double ss[3] = {1.0, 1.0, 1.0};
+      if constexpr (FOLD) {
+        ss[0] = wave_shift<kWaveShr1>(q.se[L], q.sc[L]);
+        ss[1] = q.sc[L];
+        ss[2] = wave_shift<kWaveShl1>(q.se[L], q.sc[L]);
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const bool in = q.lin[L] && (d == 0 ? i > 0 : (d == 2 ? i < n - 1 : true));
+        double a = (d == 0) ? entry<E>(K, diag) : (d == 1 ? entry<E + 1>(K, diag) : entry<E + 2>(K, diag));
+        if constexpr (FOLD) a = a * ss[d];
+        const V t = acc + V(a) * V(xs[d]);
+        acc = in ? t : acc;
+      }
+      plane_terms<P, L + 1>(i, K, diag, q, acc);
+    }
+  }
+
+  __device__ __forceinline__ double diag_of(double dsum) const {
     return (dsum + hsum) + shift;
   }
 
   // a_ii of row `row` (the unscaled operator).
   __device__ __forceinline__ double diagonal(int32_t row) const {
     const int32_t i = row % n, jk = row / n, j = jk % n, k = jk / n;
-    double K[2][2][2], kb[27];
+    double K[2][2][2];
     cells(i, j, k, K);
     double dsum = 0.0;
-    kbars<0>(K, kb, dsum);
-    return diag_of(kb, dsum);
+    kbars<0>(K, dsum);
+    return diag_of(dsum);
   }
 
   // Row `row` of A x (all 64 lanes of the row's 64-row block call it together;
@@ -1010,13 +1033,36 @@ struct Conv27Op {
     const int32_t b0 = row - lane;
     const int32_t rc = min(row, n * n * n - 1);  // rows past the grid compute a discarded copy of the last
     const int32_t i = rc % n, jk = rc / n, j = jk % n, k = jk / n;
-    double K[2][2][2], kb[27];
+    double K[2][2][2];
     cells(i, j, k, K);
+    Plane<X> q0, q1;
+    load_plane<0>(rc, b0, lane, j, k, x, q0);
     double dsum = 0.0;
-    kbars<0>(K, kb, dsum);
-    const double diag = diag_of(kb, dsum);
+    kbars<0>(K, dsum);
+    const double diag = diag_of(dsum);
+    // The diagonal needs every kbar before the row's middle term.  Keeping the
+    // 26 of them from here took 54 registers; they are formed again, plane by
+    // plane, from the 8 cells.  One plane's loads are in flight while the one
+    // before it is summed: all nine lines' at once held 165 registers, three
+    // waves per SIMD.
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) asm volatile("" : "+v"(K[c][b][a]));
     V acc = V(0);
-    line<0>(rc, b0, lane, i, j, k, kb, diag, x, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    load_plane<1>(rc, b0, lane, j, k, x, q1);
+    plane_terms<0, 0>(i, K, diag, q0, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    load_plane<2>(rc, b0, lane, j, k, x, q0);
+    plane_terms<1, 0>(i, K, diag, q1, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    plane_terms<2, 0>(i, K, diag, q0, acc);
+    // not to be moved behind the caller's test of `valid`: the lane shifts stay
+    // in front of it, and every plane's values would be held until then
+    asm volatile("" : "+v"(acc));
     return valid ? acc : V(0);
   }
 };

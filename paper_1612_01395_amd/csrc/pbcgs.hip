@@ -563,6 +563,7 @@ int true_relres(pbcgs_ctx_t ctx, const Op& op, const Args& a0, double rho0, doub
 // ---------------------------------------------------------------------------
 constexpr int32_t kManyRows = 1 << 21;  // see Driver::take_many
 constexpr int kManyR = 8;
+constexpr int kFirstChunk = 8;  // iterations of a solve's first two chunks
 // MP: precision form (Op is the binary32 operator, Op64 the binary64 one).
 template <class Op, int PC, class Op64 = Op, bool MP = false>
 struct Driver {
@@ -1074,6 +1075,8 @@ struct Driver {
       for (;;) {
         while (!stop && launched < o.maxit && npend < 2) {
           int m = (int)std::min<int64_t>(check, o.maxit - launched);
+          // the first polls come early: a solve of 20 iterations is not given 64
+          if (o.check_every <= 0 && launched < 2 * kFirstChunk) m = std::min(m, kFirstChunk);
           if (rate < 0.0 && o.tol > 0.0 && last_rel > 0.0) {
             const double need = (std::log(o.tol) - std::log(last_rel)) / rate;  // from the last poll
             const int64_t ahead = launched - last_it;                           // queued since then
