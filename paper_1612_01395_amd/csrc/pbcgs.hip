@@ -97,6 +97,9 @@ struct pbcgs_ctx_s {
   int coop = -1;            // device supports cooperative launches (-1: not asked yet)
   double* bigpart = nullptr;     // partial sums of launches of more than kMaxG workgroups
   size_t bigpart_cap = 0;        // doubles
+  unsigned char* bres = nullptr;  // batched resident solves: tables and vectors
+  size_t bres_cap = 0;            // bytes
+  bool streamed_only = false;     // the autotuners time the streamed kernels
   unsigned char* res = nullptr;  // resident solves: exchange words, then kResAux bytes
   int32_t* hflag = nullptr; // pinned host copy
   double* part = nullptr;   // PB_COUNT buffers of kMaxD * kMaxG partial sums
@@ -354,6 +357,13 @@ void poison(pbcgs_ctx_t ctx, void* p, size_t bytes) {
   const int64_t words = (int64_t)(bytes / 4);
   k_poison<<<debug_blocks(words), kDebugWG, 0, ctx->stream>>>(static_cast<uint32_t*>(p), words);
 }
+
+// The autotuners time launch shapes of the streamed kernels.
+struct StreamedScope {
+  pbcgs_ctx_t c;
+  explicit StreamedScope(pbcgs_ctx_t c_) : c(c_) { c->streamed_only = true; }
+  ~StreamedScope() { c->streamed_only = false; }
+};
 
 // Switches the poisoning hook on for one call (off again on every return).
 struct PoisonScope {
@@ -659,7 +669,7 @@ struct Driver {
   // are folded by one small kernel before they are consumed.
   bool take_many() {
     const int mode = env_int("PBCGS_MANY", -1);
-    if (mode == 0 || ctx->noalloc || (mode < 0 && a.n <= kManyRows)) return false;
+    if (mode == 0 || ctx->noalloc || ctx->streamed_only || (mode < 0 && a.n <= kManyRows)) return false;
     if (std::getenv("PBCGS_R") || std::getenv("PBCGS_GTARGET")) return false;
     const int R = mode > 0 ? mode : kManyR;
     const int64_t G = ((int64_t)a.n + 256 * (int64_t)R - 1) / (256 * (int64_t)R);
@@ -1183,16 +1193,16 @@ struct Driver {
 // environment), the perturbation hook and the allocation-free entry point keep
 // those.  PBCGS_PERSIST=0 never takes the resident form, =1 also with the
 // environment's switches set.
-bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o) {
-  if (ctx->noalloc || ctx->perturb_iter >= 0 || o.precision != PBCGS_FP64 || (o.flags & (1 | 2 | 8 | 16))) return false;
+bool resident_options(pbcgs_ctx_t ctx, const pbcgs_opts& o) {
+  if (ctx->noalloc || ctx->streamed_only || ctx->perturb_iter >= 0 || o.precision != PBCGS_FP64 ||
+      (o.flags & (1 | 2 | 8 | 16)))
+    return false;
   if (!res_method(o.variant) || o.maxit > 100000000) return false;  // exchange numbers stay in 32 bits
-  const bool layout = A->kind == OP_CSR && A->ndia > 0 && A->ndia <= kResMaxND;
-  if (!layout && A->kind != OP_ST5 && A->kind != OP_ST7) return false;
   const int mode = env_int("PBCGS_PERSIST", -1);
   if (mode == 0) return false;
   if (mode < 0) {
     for (const char* e : {"PBCGS_R", "PBCGS_GTARGET", "PBCGS_VALUE_CODES", "PBCGS_XCD_MAP", "PBCGS_TWO_ROWS64",
-                          "PBCGS_DIA_CACHED"})
+                          "PBCGS_DIA_CACHED", "PBCGS_BATCH_GCAP", "PBCGS_MANY"})
       if (std::getenv(e)) return false;
   }
   if (ctx->coop < 0) {
@@ -1200,6 +1210,10 @@ bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o)
     ctx->coop = (hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && v) ? 1 : 0;
   }
   return ctx->coop == 1;
+}
+bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o) {
+  const bool layout = A->kind == OP_CSR && A->ndia > 0 && A->ndia <= kResMaxND;
+  return (layout || A->kind == OP_ST5 || A->kind == OP_ST7) && resident_options(ctx, o);
 }
 
 // The operator's structure in the resident form (values left out).
@@ -1248,6 +1262,18 @@ int resident_uniform(pbcgs_ctx_t ctx, const pbcgs_op_s* A, int pc_fold, const do
   return PBCGS_SUCCESS;
 }
 
+ResJob resident_job(const pbcgs_opts& o) {
+  ResJob j;
+  std::memset(&j, 0, sizeof j);
+  j.variant = o.variant;
+  j.rr_period = o.rr_period;
+  j.rr_max = o.rr_max;
+  j.maxit = o.maxit;
+  j.aform = alpha_form(o);
+  j.tol = o.tol;
+  return j;
+}
+
 // Runs the solve from x_0 (its folded form y_0 when `fold` is set, see
 // k_fold_x) and leaves the iterate in ctx->ws; *done = false, with nothing of
 // the caller's written, when it did not run to its end (a launch refused, or a
@@ -1256,13 +1282,7 @@ int run_resident(pbcgs_ctx_t ctx, const ResPlan& plan, const ResOp& op, const Ar
                  const double* fold_dv, double fold_ds, bool fold, pbcgs_info* info, double* rho0, bool* done) {
   hipStream_t s = ctx->stream;
   *done = false;
-  ResJob j;
-  j.variant = o.variant;
-  j.rr_period = o.rr_period;
-  j.rr_max = o.rr_max;
-  j.maxit = o.maxit;
-  j.aform = alpha_form(o);
-  j.tol = o.tol;
+  ResJob j = resident_job(o);
   j.pc = pc != PC_NONE;
   j.dinv = pc == PC_VEC ? a.dinv : nullptr;
   j.dinv_s = a.dinv_s;
@@ -1479,6 +1499,35 @@ struct BatchDriver {
     tmpl.aform = alpha_form(o_);
   }
 
+  // The resident form of the whole batch (resident.hpp); set by the caller
+  // when every system fits it.
+  const ResBatchPlan* res_plan_ = nullptr;
+  const std::vector<ResBatchSys>* res_sys = nullptr;
+
+  // Runs it; *done = false, with nothing of the caller's written, when it did
+  // not run to its end.
+  int run_resident(bool* done) {
+    hipStream_t s = ctx->stream;
+    *done = false;
+    int32_t* err = nullptr;
+    int32_t bad = 1;
+    if (res_batch_launch(*res_plan_, *res_sys, resident_job(o), ctx->bres, s, &err) != hipSuccess) {
+      (void)hipGetLastError();
+      HIP_TRY(ctx, hipStreamSynchronize(s));
+      return PBCGS_SUCCESS;
+    }
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->hflag, err, sizeof bad, hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    if (*ctx->hflag != 0) return PBCGS_SUCCESS;
+    for (int32_t k = 0; k < nsys; ++k) {
+      const ResBatchSys& y = (*res_sys)[(size_t)k];
+      HIP_TRY(ctx, hipMemcpyAsync(const_cast<double*>(y.x0), y.vecs + 3 * y.stride, sizeof(double) * (size_t)y.op.n,
+                                  hipMemcpyDeviceToDevice, s));
+    }
+    *done = true;
+    return PBCGS_SUCCESS;
+  }
+
   double* part(int which) const { return ctx->bpart + (size_t)which * kMaxD * totalG; }
 
   Args L(int pin, int pout, bool first = false) {
@@ -1603,12 +1652,9 @@ struct BatchDriver {
     return PBCGS_SUCCESS;
   }
 
-  int run(pbcgs_info* infos) {
+  // The iterations in launches over the whole batch.
+  int run_streamed(bool use_graph, int check, size_t nst) {
     hipStream_t s = ctx->stream;
-    const bool use_graph = !(o.flags & 1);
-    const int check = o.check_every > 0 ? o.check_every : 8;
-    const size_t nst = (size_t)nsys * 4;
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
     if constexpr (kTwo) kb_dia_fill<<<totalG, kWG, 0, s>>>(ctx->bsys, ctx->bmap);
     kb_init_state<<<(nsys + 63) / 64, 64, 0, s>>>(ctx->bsys, nsys, 0, o.tol);
     q = 0;
@@ -1644,6 +1690,25 @@ struct BatchDriver {
     }
     finish(launched);
     HIP_TRY(ctx, hipGetLastError());
+    return PBCGS_SUCCESS;
+  }
+
+  int run(pbcgs_info* infos) {
+    hipStream_t s = ctx->stream;
+    const bool use_graph = !(o.flags & 1);
+    const int check = o.check_every > 0 ? o.check_every : 8;
+    const size_t nst = (size_t)nsys * 4;
+    HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
+    bool done = false;
+    if (res_plan_) {
+      q = 0;  // the final states are in slot 0
+      const int rc = run_resident(&done);
+      if (rc != PBCGS_SUCCESS) return rc;
+    }
+    if (!done) {
+      const int rc = run_streamed(use_graph, check, nst);
+      if (rc != PBCGS_SUCCESS) return rc;
+    }
     HIP_TRY(ctx, hipEventRecord(ctx->ev_stop, s));
     std::vector<DevState> fin(nst);
     HIP_TRY(ctx, hipMemcpyAsync(fin.data(), ctx->bst, nst * sizeof(DevState), hipMemcpyDeviceToHost, s));
@@ -1794,6 +1859,7 @@ int pbcgs_ctx_destroy(pbcgs_ctx_t ctx) {
   if (ctx->part) (void)hipFree(ctx->part);
   if (ctx->flag) (void)hipFree(ctx->flag);
   if (ctx->res) (void)hipFree(ctx->res);
+  if (ctx->bres) (void)hipFree(ctx->bres);
   if (ctx->bigpart) (void)hipFree(ctx->bigpart);
   if (ctx->st) (void)hipFree(ctx->st);
   if (ctx->hst) (void)hipHostFree(ctx->hst);
@@ -2873,9 +2939,52 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
   HIP_TRY(ctx, hipMemcpyAsync(ctx->bsys, desc.data(), desc.size() * sizeof(SysDesc), hipMemcpyHostToDevice, ctx->stream));
   HIP_TRY(ctx, hipMemcpyAsync(ctx->bmap, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host tables may go away after this
-  const int st = dia       ? BatchDriver<DiaOpB>(ctx, o, nsys, (int32_t)totalG).run(infos)
-                 : compact ? BatchDriver<CsrOp16>(ctx, o, nsys, (int32_t)totalG).run(infos)
-                           : BatchDriver<CsrOp>(ctx, o, nsys, (int32_t)totalG).run(infos);
+  // Every system within the resident form: the batch runs in it, and only the
+  // true residuals are left to the launches over the whole batch.
+  std::vector<ResBatchSys> rsys;
+  ResBatchPlan rplan;
+  if (dia && resident_options(ctx, o)) {
+    size_t vecs = 0;
+    for (int32_t k = 0; k < nsys; ++k) {
+      ResBatchSys y;
+      std::memset(&y, 0, sizeof y);
+      y.op = resident_structure(A[k]);
+      y.rp = A[k]->rp;
+      y.ci = A[k]->ci;
+      y.va = A[k]->va;
+      y.b = b[k];
+      y.x0 = x[k];
+      y.stride = (int64_t)padded(A[k]->n) + (int64_t)kResVecPad;
+      y.st = ctx->bst + (size_t)k * 4;
+      vecs += (size_t)kResBatchVecs * (size_t)y.stride;
+      rsys.push_back(y);
+    }
+    rplan = res_batch_plan(rsys, ctx->cus);
+    if (rplan.ok) {
+      const size_t tables = (res_batch_bytes(rplan, nsys) + 255) & ~(size_t)255;
+      rc = grow(ctx, ctx->bres, ctx->bres_cap, tables + vecs * sizeof(double), "resident batch");
+      if (rc != PBCGS_SUCCESS) return rc;
+      double* v = reinterpret_cast<double*>(ctx->bres + tables);
+      poison(ctx, v, vecs * sizeof(double));
+      for (ResBatchSys& y : rsys) {
+        y.vecs = v;
+        v += kResBatchVecs * y.stride;
+      }
+      bool uniform = false;
+      HIP_TRY(ctx, res_batch_uniform(rsys, ctx->bres, ctx->stream, &uniform));
+      rplan.ok = uniform;
+    }
+  }
+  auto run = [&](auto driver) -> int {
+    if (rplan.ok) {
+      driver.res_plan_ = &rplan;
+      driver.res_sys = &rsys;
+    }
+    return driver.run(infos);
+  };
+  const int st = dia && !rplan.ok ? run(BatchDriver<DiaOpB>(ctx, o, nsys, (int32_t)totalG))
+                 : compact        ? run(BatchDriver<CsrOp16>(ctx, o, nsys, (int32_t)totalG))
+                                  : run(BatchDriver<CsrOp>(ctx, o, nsys, (int32_t)totalG));
   if (st >= 0)
     for (int32_t k = 0; k < nsys; ++k) {
       infos[k].rows_per_wave_blocks = desc[(size_t)k].R;
@@ -2893,6 +3002,7 @@ int pbcgs_tune(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, const pbcgs_opts*
       (opts->precision != PBCGS_FP64 && opts->precision != PBCGS_FP32_RR64))
     return fail(ctx, PBCGS_ERR_INVALID_ARG, "unknown variant or precision");
   DeviceGuard guard(ctx->device);
+  StreamedScope streamed(ctx);
   std::memset(rep, 0, sizeof *rep);
   double* xs = nullptr;
   if (hipMalloc(&xs, sizeof(double) * (size_t)A->n) != hipSuccess) return fail(ctx, PBCGS_ERR_ALLOC, "tune scratch");
@@ -3009,6 +3119,7 @@ int pbcgs_tune_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, const
   // for its first iterations.
   const bool complete = (iters == 0);
   DeviceGuard guard(ctx->device);
+  StreamedScope streamed(ctx);
   std::memset(rep, 0, sizeof *rep);
   size_t tot = 0;
   for (int32_t k = 0; k < nsys; ++k) {

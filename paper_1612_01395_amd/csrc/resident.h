@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace pbcgs {
 
 struct DevState;
@@ -72,6 +74,47 @@ hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, co
 inline double* res_x(const ResJob& j) { return j.vecs + 3 * j.stride; }
 
 hipError_t res_launch(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);
+
+// ---- batches ----
+// A batched solve packs its systems into cooperative launches of at most one
+// workgroup per compute unit (kResBatchK rows per thread, one value per
+// diagonal, every diagonal within the windows).
+struct ResBatchSys {  // what the caller knows of a system
+  ResOp op;           // structure; c after res_batch_uniform
+  const int32_t* rp;
+  const int32_t* ci;
+  const double* va;
+  const double* b;
+  const double* x0;
+  double* vecs;       // kResBatchVecs vectors of `stride` doubles
+  int64_t stride;
+  DevState* st;
+};
+constexpr int kResBatchVecs = 4;    // three exchange buffers and x
+
+// Launches of a batch: each a list of systems with their first workgroup.
+struct ResBatchPlan {
+  bool ok = false;
+  int nd = 0;                       // slots: 5 or 7
+  std::vector<std::vector<int>> launches;
+  std::vector<int> G, H;            // per system
+};
+ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus);
+
+// Device bytes of a batch's tables (descriptors, maps, words, uniform values).
+size_t res_batch_bytes(const ResBatchPlan& p, int nsys);
+
+// Uploads the descriptors of res_uniform for every system, runs it and reads
+// the values into sys[k].op.c; *uniform: every system has one value per
+// diagonal.  Synchronises the stream.
+hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStream_t s, bool* uniform);
+
+// Queues the launches; *err_word receives the device address of the word that
+// is nonzero afterwards when a wait timed out.  x of system k: its vecs + 3 stride.
+hipError_t res_batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, void* tables,
+                            hipStream_t s, int32_t** err_word);
+hipError_t res_launch_batch_pipe(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s);
+hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s);
 
 // per method: its kernels live in a translation unit of their own
 hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);

@@ -4,6 +4,8 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
+#include <cstring>
+#include <vector>
 
 #include "../../include/pbcgs.h"
 #include "resident.hpp"
@@ -115,7 +117,7 @@ __device__ __forceinline__ u64 uniform_bits(const UniformArgs& u, int32_t k) {
 
 // Reference value of every diagonal: its first entry in the 8192 rows around
 // the middle (a diagonal with none there counts as varying).
-__global__ __launch_bounds__(1024) void k_uniform_ref(UniformArgs u) {
+__device__ __forceinline__ void uniform_ref(const UniformArgs& u) {
   __shared__ int first[kResMaxND];
   if (threadIdx.x < kResMaxND) first[threadIdx.x] = INT32_MAX;
   __syncthreads();
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(1024) void k_uniform_ref(UniformArgs u) {
 }
 
 // Every entry against its diagonal's reference.
-__global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) {
+__device__ __forceinline__ void uniform_check(const UniformArgs& u) {
   if (*u.flag) return;
   u64 ref[kResMaxND];
 #pragma unroll
@@ -158,6 +160,9 @@ __global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) {
   if (!same) *u.flag = 1;
 }
 
+__global__ __launch_bounds__(1024) void k_uniform_ref(UniformArgs u) { uniform_ref(u); }
+__global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) { uniform_check(u); }
+
 }  // namespace
 
 hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, const double* va, const double* dinv,
@@ -168,6 +173,184 @@ hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, co
   k_uniform_ref<<<1, 1024, 0, s>>>(u);
   k_uniform_check<<<std::min((op.n + 255) / 256, 2048), 256, 0, s>>>(u);
   return hipGetLastError();
+}
+
+// ---- batches ----
+namespace {
+
+// Layout of a batch's tables.
+struct BatchTables {
+  size_t uni, ref, err, words, sys, map, bytes;
+  BatchTables(int nsys, int maps) {
+    auto take = [this](size_t b) {
+      const size_t at = bytes;
+      bytes += (b + 255) & ~(size_t)255;
+      return at;
+    };
+    bytes = 0;
+    uni = take(sizeof(UniformArgs) * (size_t)nsys);
+    ref = take(kResAux * (size_t)nsys);
+    err = take(sizeof(int32_t));
+    words = take(sizeof(u64) * (size_t)kResWords * nsys);
+    sys = take(sizeof(ResSys<7>) * (size_t)nsys);
+    map = take(sizeof(int2) * (size_t)maps);
+  }
+};
+
+__global__ __launch_bounds__(1024) void kb_uniform_ref(const UniformArgs* us) { uniform_ref(us[blockIdx.x]); }
+__global__ __launch_bounds__(256) void kb_uniform_check(const UniformArgs* us) { uniform_check(us[blockIdx.y]); }
+
+template <int ND>
+__global__ __launch_bounds__(256) void kb_res_init(const ResSys<ND>* sys) {
+  const ResArgs& a = sys[blockIdx.y].a;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < kResWords) a.words[i] = 0;
+  if (i == 0) {
+    *a.err = 0;
+    a.st->status = -1;
+  }
+}
+
+template <int ND>
+hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, char* base,
+                        const BatchTables& t, hipStream_t s) {
+  const int nsys = (int)sys.size();
+  std::vector<ResSys<ND>> h((size_t)nsys);
+  for (int k = 0; k < nsys; ++k) {
+    const ResBatchSys& y = sys[(size_t)k];
+    ResJob j = opts;
+    j.pc = false;
+    j.dinv = nullptr;
+    j.dinv_s = 0.0;
+    j.hist = nullptr;
+    j.b = y.b;
+    j.x0 = y.x0;
+    j.vecs = y.vecs;
+    j.stride = y.stride;
+    j.words = reinterpret_cast<u64*>(base + t.words) + (size_t)k * kResWords;
+    j.err = reinterpret_cast<int32_t*>(base + t.err);
+    j.st = y.st;
+    ResPlan q;
+    q.K = kResBatchK;
+    q.G = p.G[(size_t)k];
+    q.H = p.H[(size_t)k];
+    h[(size_t)k].op = res_op<ND>(y.op);
+    h[(size_t)k].a = res_args(q, j);
+  }
+  std::vector<int2> map;
+  std::vector<size_t> first;
+  for (const auto& l : p.launches) {
+    first.push_back(map.size());
+    for (int k : l)
+      for (int g = 0; g < p.G[(size_t)k]; ++g) map.push_back(int2{k, g});
+  }
+  const ResSys<ND>* dsys = reinterpret_cast<const ResSys<ND>*>(base + t.sys);
+  int2* dmap = reinterpret_cast<int2*>(base + t.map);
+  hipError_t e = hipMemcpyAsync(base + t.sys, h.data(), sizeof(ResSys<ND>) * h.size(), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(dmap, map.data(), sizeof(int2) * map.size(), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go away
+  if (e != hipSuccess) return e;
+  kb_res_init<ND><<<dim3((kResWords + 255) / 256, (unsigned)nsys), 256, 0, s>>>(dsys);
+  for (size_t l = 0; l < p.launches.size(); ++l) {
+    int W = 0, H = 0;
+    for (int k : p.launches[l]) {
+      W += p.G[(size_t)k];
+      H = std::max(H, p.H[(size_t)k]);
+    }
+    const size_t lds = res_lds(kResBatchK, H);
+    e = opts.variant == PBCGS_BICGSTAB ? res_launch_batch_bicg(ND, dsys, dmap + first[l], W, lds, s)
+                                       : res_launch_batch_pipe(ND, dsys, dmap + first[l], W, lds, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Largest systems first, each into the first launch with room: they iterate
+// longest, and the small ones fill the workgroups beside them.
+ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus) {
+  ResBatchPlan p;
+  const int maxg = std::min(cus, kResMaxG);
+  std::vector<int> order;
+  p.nd = 5;
+  for (size_t k = 0; k < sys.size(); ++k) {
+    const ResOp& op = sys[k].op;
+    if (op.nd < 1 || op.nd > kResMaxND || op.n < 1) return p;
+    if (op.nd > 5) p.nd = 7;
+    int64_t H = 0;
+    for (int d = 0; d < op.nd; ++d) H = std::max(H, std::abs((int64_t)op.off[d]));
+    H = (H + 1) & ~1ll;
+    const int64_t G = (op.n + kResT * kResBatchK - 1) / (kResT * kResBatchK);
+    if (G > maxg || (int64_t)res_lds(kResBatchK, 0) + 4 * H * 8 > 160 * 1024 - 4096) return p;
+    p.G.push_back((int)G);
+    p.H.push_back((int)H);
+    order.push_back((int)k);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sys[(size_t)a].op.n > sys[(size_t)b].op.n; });
+  std::vector<int> used;
+  for (int k : order) {
+    size_t l = 0;
+    while (l < used.size() && used[l] + p.G[(size_t)k] > maxg) ++l;
+    if (l == used.size()) {
+      used.push_back(0);
+      p.launches.emplace_back();
+    }
+    used[l] += p.G[(size_t)k];
+    p.launches[l].push_back(k);
+  }
+  p.ok = true;
+  return p;
+}
+
+size_t res_batch_bytes(const ResBatchPlan& p, int nsys) {
+  int maps = 0;
+  for (int g : p.G) maps += g;
+  return BatchTables(nsys, maps).bytes;
+}
+
+hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStream_t s, bool* uniform) {
+  const int nsys = (int)sys.size();
+  const BatchTables t(nsys, 0);
+  char* base = static_cast<char*>(tables);
+  std::vector<UniformArgs> h((size_t)nsys);
+  int32_t nmax = 0;
+  for (int k = 0; k < nsys; ++k) {
+    const ResBatchSys& y = sys[(size_t)k];
+    u64* ref = reinterpret_cast<u64*>(base + t.ref + kResAux * (size_t)k);
+    h[(size_t)k] = {y.op.mask, y.rp, y.ci, y.va, nullptr, 0.0, ref, reinterpret_cast<int32_t*>(ref + kResMaxND),
+                    y.op.n, y.op.nd, 1};
+    nmax = std::max(nmax, y.op.n);
+  }
+  std::vector<unsigned char> out(kResAux * (size_t)nsys);
+  const UniformArgs* d = reinterpret_cast<const UniformArgs*>(base + t.uni);
+  hipError_t e = hipMemcpyAsync(base + t.uni, h.data(), sizeof(UniformArgs) * h.size(), hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return e;
+  kb_uniform_ref<<<nsys, 1024, 0, s>>>(d);
+  kb_uniform_check<<<dim3((unsigned)std::min((nmax + 1023) / 1024, 256), (unsigned)nsys), 256, 0, s>>>(d);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(out.data(), base + t.ref, out.size(), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return e;
+  *uniform = true;
+  for (int k = 0; k < nsys; ++k) {
+    int32_t flag;
+    std::memcpy(&flag, &out[kResAux * (size_t)k + 8 * kResMaxND], sizeof flag);
+    *uniform = *uniform && flag == 0;
+    std::memcpy(sys[(size_t)k].op.c, &out[kResAux * (size_t)k], sizeof(double) * kResMaxND);
+  }
+  return hipSuccess;
+}
+
+hipError_t res_batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, void* tables,
+                            hipStream_t s, int32_t** err_word) {
+  int maps = 0;
+  for (int g : p.G) maps += g;
+  const BatchTables t((int)sys.size(), maps);
+  char* base = static_cast<char*>(tables);
+  *err_word = reinterpret_cast<int32_t*>(base + t.err);
+  if (p.nd <= 5) return batch_launch<5>(p, sys, opts, base, t, s);
+  return batch_launch<7>(p, sys, opts, base, t, s);
 }
 
 bool res_method(int32_t variant) { return variant != PBCGS_CA_BICGSTAB; }

@@ -54,6 +54,7 @@ typedef unsigned U4 __attribute__((ext_vector_type(4)));
 constexpr int kResSpin = 1 << 19;  // polls before a wait gives up (about a second)
 constexpr int kResFront = 2;       // doubles before row 0 in an exchange buffer
 constexpr int kSc1 = 16;           // buffer cache policy: agent scope
+constexpr int kResBatchK = 8;      // rows per thread of batched launches
 
 template <int ND>
 struct ResOpT {
@@ -104,6 +105,19 @@ __device__ __forceinline__ void uniform(State& s) {
   s.iters = uniform(s.iters);
 }
 
+// XCD-contiguous index of a launch's workgroup: workgroup b runs on XCD b % 8.
+__device__ __forceinline__ int xcd_index() {
+  const int b = (int)blockIdx.x, G = (int)gridDim.x, q = G >> 3, r = G & 7, x = b & 7;
+  return x * q + min(x, r) + (b >> 3);
+}
+
+// One system of a batched launch.
+template <int ND>
+struct ResSys {
+  ResOpT<ND> op;
+  ResArgs a;
+};
+
 // What the kernels of every method share: the thread's place, the windows in
 // LDS, the exchange and the product.  KP = pairs per thread, NW = waves.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
@@ -123,9 +137,10 @@ struct Res {
   const ResArgs& a;
   Shared& sh;
   double* sm;        // two windows: rows [base - H, base + 512 K + H) of two gathered vectors
+  const int wg;      // the system's workgroup
   uint32_t ix;       // exchange buffer of each window's vector (bits 0-7, 8-15), then the spare one
   int32_t n, base, row0, li0;
-  int wg, lane, wave, t;
+  int lane, wave, t;
   unsigned epoch = 0;
   // per pair: the diagonals its rows hold (row 0 in bits 0-7, row 1 in bits
   // 8-15; two pairs to a word), and those every row of its 128-row block holds
@@ -133,14 +148,11 @@ struct Res {
   uint32_t mk[(KP + 1) / 2];
   uint32_t all[(KP + 3) / 4];
 
-  __device__ __forceinline__ Res(const ResOpT<ND>& op_, const ResArgs& a_, Shared& sh_, double* sm_)
-      : op(op_), a(a_), sh(sh_), sm(sm_) {
+  __device__ __forceinline__ Res(const ResOpT<ND>& op_, const ResArgs& a_, Shared& sh_, double* sm_, int wg_)
+      : op(op_), a(a_), sh(sh_), sm(sm_), wg(wg_) {
     t = threadIdx.x;
     lane = t & 63;
     wave = t >> 6;
-    // XCD-contiguous indices: workgroup b runs on XCD b % 8
-    const int b = (int)blockIdx.x, q = a.G >> 3, r = a.G & 7, x = b & 7;
-    wg = x * q + min(x, r) + (b >> 3);
     n = op.n;
     base = wg * (kResT * K);
     row0 = base + wave * 64 * K + 2 * lane;
@@ -441,7 +453,7 @@ struct Res {
       for (int j = 0; j < KP; ++j)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, x.r[j]), rsrc_x(x), row(j) * 8, 0, 0);
     }
-    if (leader()) store_state(a.st, st);
+    if (wg == 0 && t == 0) store_state(a.st, st);
   }
   __device__ __forceinline__ State start() const {
     State st;
@@ -574,6 +586,18 @@ inline hipError_t res_go(void (*k)(ResOpT<ND>, ResArgs), int K, const ResPlan& p
   if (e != hipSuccess) return e;
   void* args[] = {&o, &a};
   return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k), dim3((unsigned)p.G), dim3(kResT), args,
+                                    (unsigned)lds, s);
+}
+
+template <int ND>
+inline hipError_t res_go_batch(void (*k)(const ResSys<ND>*, const int2*), const void* sys, const int2* map, int workgroups,
+                               size_t lds, hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds);
+  if (e != hipSuccess) return e;
+  const ResSys<ND>* p = static_cast<const ResSys<ND>*>(sys);
+  void* args[] = {&p, &map};
+  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k), dim3((unsigned)workgroups), dim3(kResT), args,
                                     (unsigned)lds, s);
 }
 

@@ -12,12 +12,12 @@ namespace {
 // r0, r, s, y and x, with Jacobi also p and q.  Window 0 holds p^ (p), window
 // 1 q^ (q).
 template <int K, int ND, bool FAR, bool UNI, bool PC>
-__global__ __launch_bounds__(kResT) void k_res_bicg(ResOpT<ND> op, ResArgs a) {
+__device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
   using R = Res<K, ND, FAR, UNI, PC>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
-  R g(op, a, sh, sm);
+  R g(op, a, sh, sm, wg);
   constexpr int P = 0, Q = 1;
 
   D2 r0[KP], r[KP], s[KP], y[KP];
@@ -141,6 +141,22 @@ __global__ __launch_bounds__(kResT) void k_res_bicg(ResOpT<ND> op, ResArgs a) {
   g.finish(x, st);
 }
 
+template <int K, int ND, bool FAR, bool UNI, bool PC>
+__global__ __launch_bounds__(kResT) void k_res_bicg(ResOpT<ND> op, ResArgs a) {
+  res_bicg_solve<K, ND, FAR, UNI, PC>(op, a, xcd_index());
+}
+
+// Workgroup i of the launch (XCD-contiguous) belongs to system map[i].x and is
+// its workgroup map[i].y.
+template <int ND>
+__global__ __launch_bounds__(kResT) void kb_res_bicg(const ResSys<ND>* __restrict__ sys, const int2* __restrict__ map) {
+  const int i = xcd_index();
+  const int k = uniform(map[i].x);
+  const ResOpT<ND> op = sys[k].op;
+  const ResArgs a = sys[k].a;
+  res_bicg_solve<kResBatchK, ND, false, true, false>(op, a, uniform(map[i].y));
+}
+
 }  // namespace
 
 hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
@@ -149,6 +165,11 @@ hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, h
     return res_go<ND>(&k_res_bicg<K, ND, decltype(far)::value, decltype(uni)::value, decltype(pc)::value>, K, p, op, j,
                       s);
   });
+}
+
+hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s) {
+  if (nd <= 5) return res_go_batch<5>(&kb_res_bicg<5>, sys, map, workgroups, lds, s);
+  return res_go_batch<7>(&kb_res_bicg<7>, sys, map, workgroups, lds, s);
 }
 
 }  // namespace pbcgs

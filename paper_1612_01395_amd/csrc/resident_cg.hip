@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
-  R g(op, a, sh, sm);
+  R g(op, a, sh, sm, xcd_index());
   constexpr int P = 0, T = 1;
 
   D2 r[KP], s[KP];
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
-  R g(op, a, sh, sm);
+  R g(op, a, sh, sm, xcd_index());
   constexpr int U = 0, T = 1;
 
   D2 r[KP], p[KP], s[KP], w[KP];
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
-  R g(op, a, sh, sm);
+  R g(op, a, sh, sm, xcd_index());
 
   D2 r[KP], p[KP], s[KP], z[KP];
   D2 w[PC ? KP : 1], q[PC ? KP : 1], u[PC ? KP : 1];

@@ -20,12 +20,12 @@ __device__ __forceinline__ bool res_rr_due(const ResArgs& a, int64_t i) {
 // 0 holds w^ (w), window 1 z^ (z).  Measured on one system (folded Jacobi):
 // see the table of resident sizes at res_plan.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
-__global__ __launch_bounds__(kResT) void k_res_pipe(ResOpT<ND> op, ResArgs a) {
+__device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
   using R = Res<K, ND, FAR, UNI, PC>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
-  R g(op, a, sh, sm);
+  R g(op, a, sh, sm, wg);
   constexpr int W = 0, Z = 1;
   typename R::X x, r0;
   D2 r[KP], s[KP], ph[KP], tv[KP];
@@ -310,6 +310,22 @@ __global__ __launch_bounds__(kResT) void k_res_pipe(ResOpT<ND> op, ResArgs a) {
   g.finish(x, st);
 }
 
+template <int K, int ND, bool FAR, bool UNI, bool PC>
+__global__ __launch_bounds__(kResT) void k_res_pipe(ResOpT<ND> op, ResArgs a) {
+  res_pipe_solve<K, ND, FAR, UNI, PC>(op, a, xcd_index());
+}
+
+// Workgroup i of the launch (XCD-contiguous) belongs to system map[i].x and is
+// its workgroup map[i].y.
+template <int ND>
+__global__ __launch_bounds__(kResT) void kb_res_pipe(const ResSys<ND>* __restrict__ sys, const int2* __restrict__ map) {
+  const int i = xcd_index();
+  const int k = uniform(map[i].x);
+  const ResOpT<ND> op = sys[k].op;
+  const ResArgs a = sys[k].a;
+  res_pipe_solve<kResBatchK, ND, false, true, false>(op, a, uniform(map[i].y));
+}
+
 }  // namespace
 
 hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
@@ -318,6 +334,11 @@ hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, h
     return res_go<ND>(&k_res_pipe<K, ND, decltype(far)::value, decltype(uni)::value, decltype(pc)::value>, K, p, op, j,
                       s);
   });
+}
+
+hipError_t res_launch_batch_pipe(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s) {
+  if (nd <= 5) return res_go_batch<5>(&kb_res_pipe<5>, sys, map, workgroups, lds, s);
+  return res_go_batch<7>(&kb_res_pipe<7>, sys, map, workgroups, lds, s);
 }
 
 }  // namespace pbcgs

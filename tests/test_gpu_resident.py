@@ -140,3 +140,32 @@ def test_same_bits_as_the_streamed_kernels_by_default(monkeypatch):
             assert (info.iters, info.n_rr, info.status) == (ref.iters, ref.n_rr, ref.status), (dims, variant)
             assert same(host(x), host(y)) and same(host(info.history), host(ref.history)), (dims, variant)
             assert same([info.relres_rec, info.relres_true], [ref.relres_rec, ref.relres_true]), (dims, variant)
+
+
+@pytest.mark.parametrize("variant", ["pbicgstab_rr", "bicgstab"])
+def test_batch_over_several_launches(variant, monkeypatch):
+    """A batch of more workgroups than one launch holds, five and seven
+    diagonals together, one to 64 workgroups a system; then with one system
+    whose values vary, which takes the streamed kernels."""
+    require_gpu()
+    for k in ("PBCGS_RESIDENT_ROWS", "PBCGS_BATCH_GCAP"):
+        monkeypatch.delenv(k, raising=False)
+    ops, bs = [], []
+    for n in (512, 500, 333, 64, 65, 1, 2, 400, 90, 511, 128, 300):
+        ops.append(solver.csr(*solver.assemble_convdiff(2, n, 5, (20.0, 10.0))))
+    for n in (30, 3, 17):
+        ops.append(solver.csr(*solver.assemble_convdiff(3, n, 7, (50.0, 30.0, 10.0))))
+    rng = np.random.default_rng(8)
+    kw = dict(variant=variant, tol=1e-9, maxit=45, rr_period=20)
+    for varying in (False, True):
+        if varying:
+            ops.append(csr_op(band(2000, [-40, -1, 1, 40], varying=True)))
+        bs = [dev_t(rng.standard_normal(A.n)) for A in ops]
+        out = []
+        for mode in ("0", "1"):
+            monkeypatch.setenv("PBCGS_PERSIST", mode)
+            out.append(solver.solve_batched(ops, bs, **kw))
+        (xs, si), (ys, ti) = out
+        for k, (x, y, i, t) in enumerate(zip(xs, ys, si, ti)):
+            assert (i.iters, i.n_rr, i.status) == (t.iters, t.n_rr, t.status), (k, i, t)
+            assert same(host(x), host(y)) and same([i.relres_rec, i.relres_true], [t.relres_rec, t.relres_true]), k
