@@ -16,7 +16,7 @@ constexpr int kResT = 512;          // threads per workgroup: 8 x wave64
 constexpr int kResMaxG = 256;       // workgroups: one per compute unit
 constexpr int kResMaxND = 7;        // diagonals
 constexpr int kResVecs = 5;         // global vectors a launch needs (three exchange buffers, x and r0)
-constexpr int kResWords = 2 * 2 * 5 * kResMaxG;  // tagged words of two reductions in flight
+constexpr int kResWords = 4 * 2 * 5 * kResMaxG;  // tagged words of four exchanges
 constexpr size_t kResAux = 64;      // bytes of res_uniform's result: one value per diagonal, then a flag word
 constexpr size_t kResVecPad = 64;   // doubles a global vector holds beyond n
 
@@ -52,6 +52,7 @@ struct ResJob {
 struct ResPlan {
   int K = 0;      // rows per thread; 0: the operator does not fit
   int G = 0;      // workgroups
+  int reach = 0;  // workgroups on either side whose rows a product reads
   int H = 0;      // rows beyond the workgroup's own that its LDS windows hold, each side
   bool far = false;  // the first and last diagonal are read from the exchange buffers
 };

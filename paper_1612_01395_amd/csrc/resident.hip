@@ -17,8 +17,8 @@ namespace {
 // Rows per thread that `op` can run with, and its windows: the diagonals other
 // than a far first and last one must lie within H rows, and two windows of
 // 512 K + 2 H doubles must fit the 160 KB of LDS beside the kernel's 2.6 KB.
-bool res_fit(const ResOp& op, int K, bool pc, int maxg, ResPlan* p) {
-  if (K > 8 && (pc || op.va != nullptr)) return false;
+bool res_fit(const ResOp& op, int K, bool pc, bool pc16, int maxg, ResPlan* p) {
+  if (K > 8 && ((pc && !pc16) || op.va != nullptr)) return false;
   const int64_t rows = (int64_t)kResT * K;
   const int64_t G = (op.n + rows - 1) / rows;
   if (G > maxg) return false;
@@ -38,21 +38,23 @@ bool res_fit(const ResOp& op, int K, bool pc, int maxg, ResPlan* p) {
   p->G = (int)G;
   p->H = (int)H;
   p->far = far;
+  p->reach = (int)((all + rows - 1) / rows);
   return true;
 }
 
 struct MethodCost {
   int exchanges;   // per iteration
   double per_row;  // microseconds per row of a thread
+  bool pc16;       // Jacobi instances with 16 rows per thread (the registers hold them)
 };
 
 MethodCost method_cost(int32_t variant) {
   switch (variant) {
-    case PBCGS_BICGSTAB: return {5, 0.5};
-    case PBCGS_CG: return {3, 0.23};
-    case PBCGS_CGCG: return {2, 0.33};
-    case PBCGS_PIPE_CG: return {1, 0.25};
-    default: return {2, 0.9};
+    case PBCGS_BICGSTAB: return {5, 0.5, false};
+    case PBCGS_CG: return {3, 0.23, true};
+    case PBCGS_CGCG: return {2, 0.33, true};
+    case PBCGS_PIPE_CG: return {1, 0.25, false};
+    default: return {2, 0.9, false};
   }
 }
 
@@ -69,13 +71,15 @@ ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus) {
   for (int K = 2; K <= 16; K *= 2) {
     if (forced > 0 && K != forced) continue;
     ResPlan p;
-    if (!res_fit(op, K, pc, maxg, &p)) continue;
+    if (!res_fit(op, K, pc, m.pc16, maxg, &p)) continue;
     // Microseconds of an iteration that depend on the shape, fitted to runs
-    // at 41^3, 64^3, 100^3 and 150^2: an exchange takes 0.015 us more per
-    // workgroup, a row per thread 0.23 us (CG) to 0.9 us (p-BiCGStab).  At 64^3
+    // at 41^3, 64^3, 99^3, 100^3 and 150^2: an exchange takes 0.015 us more per
+    // workgroup, a row per thread 0.23 us (CG) to 0.9 us (p-BiCGStab), twice
+    // that with 16 rows (x, and r0, then come from memory).  At 64^3
     // p-BiCGStab takes 14.4 / 11.1 / 13.9 us with K = 2 / 4 / 8, BiCGStab
-    // 29.5 / 18.8 / 16.4, CG 16.5 / 10.7 / 9.0, p-CG 6.2 / 5.1 / 6.0.
-    const double c = m.exchanges * 0.015 * p.G + (pc ? 1.3 : 1.0) * m.per_row * K;
+    // 29.5 / 18.8 / 16.4, CG 16.5 / 10.7 / 9.0, p-CG 6.2 / 5.1 / 6.0; at 100^3
+    // p-BiCGStab 23.8 / 32.7 with K = 8 / 16.
+    const double c = m.exchanges * 0.015 * p.G + (pc ? 1.3 : 1.0) * (K > 8 ? 2.0 : 1.0) * m.per_row * K;
     if (best.K == 0 || c < cost) {
       best = p;
       cost = c;
@@ -234,6 +238,7 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
     q.K = kResBatchK;
     q.G = p.G[(size_t)k];
     q.H = p.H[(size_t)k];
+    q.reach = (q.H + kResT * kResBatchK - 1) / (kResT * kResBatchK);
     h[(size_t)k].op = res_op<ND>(y.op);
     h[(size_t)k].a = res_args(q, j);
   }

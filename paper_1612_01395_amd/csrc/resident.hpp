@@ -67,7 +67,7 @@ struct ResOpT {
 };
 
 struct ResArgs {
-  int32_t G, H, variant, rr_period, rr_max, maxit, aform, vec_dinv;
+  int32_t G, H, reach, variant, rr_period, rr_max, maxit, aform, vec_dinv;
   double tol, dinv_s;
   const double* dinv;
   const double* b;
@@ -120,10 +120,12 @@ struct ResSys {
 
 // What the kernels of every method share: the thread's place, the windows in
 // LDS, the exchange and the product.  KP = pairs per thread, NW = waves.
-template <int K, int ND, bool FAR, bool UNI, bool PC>
+// NEAR: exchanges without sums are barriers among neighbours (the methods with
+// such an exchange in every iteration; elsewhere the registers matter more).
+template <int K, int ND, bool FAR, bool UNI, bool PC, bool NEAR>
 struct Res {
   static constexpr int KP = K / 2;
-  static constexpr int CJ = K > 8 ? 2 : KP;  // pairs gathered at a time (bounds the registers)
+  static constexpr int CJ = KP < 2 ? KP : 2;  // pairs whose far values are in flight (bounds the registers)
   static constexpr int NWAVE = kResT / 64;
 
   struct Shared {
@@ -142,6 +144,7 @@ struct Res {
   int32_t n, base, row0, li0;
   int lane, wave, t;
   unsigned epoch = 0;
+  bool last_near = false;  // the latest exchange was among neighbours only
   // per pair: the diagonals its rows hold (row 0 in bits 0-7, row 1 in bits
   // 8-15; two pairs to a word), and those every row of its 128-row block holds
   // (uniform; four pairs to a word)
@@ -241,11 +244,15 @@ struct Res {
   // Publishes this workgroup's partial sums (lane 63 of each wave holds the
   // wave's in `part`) after its data, waits for every workgroup's, and returns
   // the totals in pairwise order "+ 0.0".  false: a wait timed out.
+  //
+  // The four waves that do not poll the sums fetch the rows around window w
+  // (the vector the next product gathers) meanwhile: they wait for the
+  // workgroups that hold those rows only.
   template <int NS>
-  __device__ __forceinline__ bool exchange(const double (&part)[NS > 0 ? NS : 1], double (&tot)[NS > 0 ? NS : 1]) {
+  __device__ __forceinline__ bool exchange(const double (&part)[NS > 0 ? NS : 1], double (&tot)[NS > 0 ? NS : 1], int w) {
     constexpr int NWD = NS > 0 ? 2 * NS : 1;  // words per workgroup
     ++epoch;
-    const int par = epoch & 1;
+    const int par = epoch & 1, slot = NEAR ? epoch & 3 : par;
     if constexpr (NS > 0) {
       if (lane == 63) {
 #pragma unroll
@@ -264,7 +271,12 @@ struct Res {
       for (int k = 0; k < NS; ++k) tot[k] = uniform(wg_sum(k) + 0.0);
       return true;
     }
-    u64* words = a.words + (size_t)par * (2 * 5 * kResMaxG);
+    // An exchange without sums is a barrier among neighbours, unless the one
+    // before was: a workgroup then never runs more than two exchanges ahead of
+    // any other, and four slots of words keep what the slowest still reads.
+    const bool near = NEAR && NS == 0 && !last_near;
+    if constexpr (NEAR) last_near = near;
+    u64* words = a.words + (size_t)slot * (2 * 5 * kResMaxG);
     if (t < NWD) {
       u64 half = 0;
       if constexpr (NS > 0) {
@@ -278,7 +290,10 @@ struct Res {
       double v[NS > 0 ? NS : 1];
 #pragma unroll
       for (int k = 0; k < NS; ++k) v[k] = 0.0;
-      if (t < a.G) {
+      // a barrier only concerns the workgroups this one reads from or is read by
+      bool mine = t < a.G;
+      if constexpr (NEAR) mine = mine && (!near || (t >= wg - a.reach && t <= wg + a.reach));
+      if (mine) {
         u64 w[NWD];
         bool ok;
         int spins = 0;
@@ -304,6 +319,21 @@ struct Res {
           for (int k = 0; k < NS; ++k) sh.lw[par][wave][k] = v[k];
         }
       }
+    } else if (w >= 0 && a.H > 0) {
+      // workgroups first .. last hold the H rows on either side
+      constexpr int rows = kResT * K;
+      const int reach = (a.H + rows - 1) / rows;
+      for (int g = max(wg - reach, 0) + lane; g <= min(wg + reach, a.G - 1); g += 64) {
+        int spins = 0;
+        while ((unsigned)(__hip_atomic_load(&words[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) != epoch) {
+          if (++spins >= kResSpin) {
+            sh.bad = 1;
+            break;
+          }
+        }
+      }
+      asm volatile("" ::: "memory");
+      halo(w);
     }
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sh.bad)) {
@@ -317,86 +347,100 @@ struct Res {
     }
     return true;
   }
-  __device__ __forceinline__ bool barrier() {
+  __device__ __forceinline__ bool barrier(int w) {
     double none[1];
-    return exchange<0>(none, none);
+    return exchange<0>(none, none, w);
   }
 
-  // The rows around the workgroup's own in window w (after the exchange that
-  // followed its put()s); rows outside [0, n) read 0 and belong to no entry.
+  // The rows around the workgroup's own in window w, by threads 256 ..  511;
+  // rows outside [0, n) read 0 and belong to no entry.
   __device__ __forceinline__ void halo(int w) {
-    if (a.G == 1) return;
     const auto r = rsrc(w);
     const int h = a.H >> 1;
-    for (int p = t; p < a.H; p += kResT) {
-      const int l = p < h ? 2 * p : kResT * K + 2 * p;  // window index: left rows, then right rows
-      *reinterpret_cast<D2*>(&win(w)[l]) = load2(r, base - a.H + l);
+    auto at = [&](int p) { return p < h ? 2 * p : kResT * K + 2 * p; };  // window index: left rows, then right rows
+    constexpr int kStep = kResT / 2, kAhead = 4;                       // loads in flight before the first is stored
+    if (a.H <= kStep) {
+      const int p = t - kStep;
+      if (p < a.H) *reinterpret_cast<D2*>(&win(w)[at(p)]) = load2(r, base - a.H + at(p));
+      return;
     }
-    __syncthreads();
+#pragma unroll 1
+    for (int p = t - kStep; p < a.H; p += kAhead * kStep) {
+      D2 v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (p + u * kStep < a.H) v[u] = load2(r, base - a.H + at(p + u * kStep));
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (p + u * kStep < a.H) *reinterpret_cast<D2*>(&win(w)[at(p + u * kStep)]) = v[u];
+    }
   }
 
   // y = A v for every pair, v in window w, handed to f(j, y_j) with j a
   // compile-time constant; load(j) is called before pair j's arithmetic, to
   // issue loads f(j) needs.  Each row sums its present diagonals in ascending
-  // order from 0.0.  The far diagonals' loads go out CJ pairs at a time; the
-  // pairs themselves are kept apart (one pair's temporaries at a time is what
-  // the registers hold beside the vectors).
+  // order from 0.0.  The far diagonals' values are loaded CJ pairs ahead, into
+  // the registers the pair before has just given up; the pairs themselves are
+  // kept apart (one pair's temporaries at a time is what the registers hold
+  // beside the vectors).
   template <class L, class F>
   __device__ __forceinline__ void product(int w, L&& load, F&& f) const {
-    each_pair<KP / CJ>([&](auto c) {
-      constexpr int c0 = decltype(c)::value * CJ;
-      const int32_t rowc = fresh(row0) + 128 * c0;
-      const double* const pc = win(w) + (fresh(li0) + 128 * c0);
-      D2 f0[CJ], f1[CJ];
-      if constexpr (FAR) {
-        const auto r = rsrc(w);
+    const int32_t r0 = fresh(row0);
+    const double* const pw = win(w) + fresh(li0);
+    D2 f0[CJ], f1[CJ];
+    const auto ex = rsrc(w);
+    if constexpr (FAR) {
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) {
-          f0[j] = load2(r, rowc + 128 * j + op.off[0]);
-          f1[j] = load2(r, rowc + 128 * j + op.off[ND - 1]);
-        }
+      for (int j = 0; j < CJ; ++j) {
+        f0[j] = load2(ex, r0 + 128 * j + op.off[0]);
+        f1[j] = load2(ex, r0 + 128 * j + op.off[ND - 1]);
       }
-      each_pair<CJ>([&](auto jc) {
-        constexpr int j = decltype(jc)::value, jj = c0 + j;
-        __builtin_amdgcn_sched_barrier(0);
-        load(std::integral_constant<int, jj>());
-        const double* p = pc + 128 * j;
-        D2 xs[ND], vs[ND];
+    }
+    each_pair<KP>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      load(jc);
+      const double* p = pw + 128 * j;
+      D2 xs[ND], vs[ND];
+#pragma unroll
+      for (int d = 0; d < ND; ++d) {
+        if (FAR && d == 0) xs[d] = f0[j % CJ];
+        else if (FAR && d == ND - 1) xs[d] = f1[j % CJ];
+        else xs[d] = *reinterpret_cast<const D2u*>(p + op.off[d]);
+      }
+      if constexpr (!UNI) {
+        const int32_t rv = min(r0 + 128 * j, (n - 1) & ~1);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) vs[d] = *reinterpret_cast<const D2*>(&op.va[(int64_t)op.vd[d] * op.ld + rv]);
+      }
+      const uint32_t m = fresh(mk[j / 2]) >> (16 * (j % 2)), u = fresh_uniform(all[j / 4]) >> (8 * (j % 4));
+      // Two forms: every row of the block holds all but the slots beside the
+      // middle one (a grid's x neighbours, which the ends of a line miss), or
+      // any slot may be missing.
+      D2 acc = {0.0, 0.0};
+      auto sum = [&](uint32_t test) {
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
-          if (FAR && d == 0) xs[d] = f0[j];
-          else if (FAR && d == ND - 1) xs[d] = f1[j];
-          else xs[d] = *reinterpret_cast<const D2u*>(p + op.off[d]);
-        }
-        if constexpr (!UNI) {
-          const int32_t rv = min(rowc + 128 * j, (n - 1) & ~1);
-#pragma unroll
-          for (int d = 0; d < ND; ++d) vs[d] = *reinterpret_cast<const D2*>(&op.va[(int64_t)op.vd[d] * op.ld + rv]);
-        }
-        const uint32_t m = fresh(mk[jj / 2]) >> (16 * (jj % 2)), u = fresh_uniform(all[jj / 4]) >> (8 * (jj % 4));
-        // Two forms: every row of the block holds all but the slots beside the
-        // middle one (a grid's x neighbours, which the ends of a line miss), or
-        // any slot may be missing.
-        D2 acc = {0.0, 0.0};
-        auto sum = [&](uint32_t test) {
-#pragma unroll
-          for (int d = 0; d < ND; ++d) {
-            const double v0 = UNI ? op.c[d] : vs[d].x, v1 = UNI ? op.c[d] : vs[d].y;
-            const double t0 = acc.x + v0 * xs[d].x, t1 = acc.y + v1 * xs[d].y;
-            if ((test >> d) & 1u) {
-              acc.x = ((m >> d) & 1u) ? t0 : acc.x;
-              acc.y = ((m >> (8 + d)) & 1u) ? t1 : acc.y;
-            } else {
-              acc.x = t0;
-              acc.y = t1;
-            }
+          const double v0 = UNI ? op.c[d] : vs[d].x, v1 = UNI ? op.c[d] : vs[d].y;
+          const double t0 = acc.x + v0 * xs[d].x, t1 = acc.y + v1 * xs[d].y;
+          if ((test >> d) & 1u) {
+            acc.x = ((m >> d) & 1u) ? t0 : acc.x;
+            acc.y = ((m >> (8 + d)) & 1u) ? t1 : acc.y;
+          } else {
+            acc.x = t0;
+            acc.y = t1;
           }
-        };
-        constexpr uint32_t full = (1u << ND) - 1u, ends = 5u << (ND / 2 - 1);
-        if (((u | ends) & full) == full) sum(ends);
-        else sum(full);
-        f(std::integral_constant<int, jj>(), acc);
-      });
+        }
+      };
+      constexpr uint32_t full = (1u << ND) - 1u, ends = 5u << (ND / 2 - 1);
+      if (((u | ends) & full) == full) sum(ends);
+      else sum(full);
+      if constexpr (FAR && j + CJ < KP) {
+        f0[j % CJ] = load2(ex, r0 + 128 * (j + CJ) + op.off[0]);
+        f1[j % CJ] = load2(ex, r0 + 128 * (j + CJ) + op.off[ND - 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      f(jc, acc);
     });
   }
   template <class F>
@@ -552,6 +596,7 @@ inline ResArgs res_args(const ResPlan& p, const ResJob& j) {
   ResArgs a = {};
   a.G = p.G;
   a.H = p.H;
+  a.reach = p.reach;
   a.variant = j.variant;
   a.rr_period = j.rr_period;
   a.rr_max = j.rr_max;
@@ -602,12 +647,13 @@ inline hipError_t res_go_batch(void (*k)(const ResSys<ND>*, const int2*), const 
 }
 
 // Calls go<K, ND, FAR, UNI, PC>() for the plan's instance.
-template <class L>
+// PC16: the method has Jacobi instances with K = 16.
+template <bool PC16, class L>
 inline hipError_t res_dispatch(const ResPlan& p, const ResOp& op, const ResJob& j, L go) {
   const bool uni = op.va == nullptr;
   auto with_pc = [&](auto k, auto nd, auto far, auto u) -> hipError_t {
     constexpr int K = decltype(k)::value;
-    if constexpr (K <= 8) {
+    if constexpr (K <= 8 || PC16) {
       if (j.pc) return go(k, nd, far, u, std::true_type());
     }
     if (j.pc) return hipErrorInvalidValue;

@@ -13,7 +13,7 @@ namespace {
 // 1 q^ (q).
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
-  using R = Res<K, ND, FAR, UNI, PC>;
+  using R = Res<K, ND, FAR, UNI, PC, true>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
@@ -27,8 +27,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
 
   // r_0 = p_0 = b - A x_0
   g.load_x0(x, Q);
-  if (!g.barrier()) return;
-  g.halo(Q);
+  if (!g.barrier(Q)) return;
   double g0[1];
   {
     typename R::template Tree<1> tr(sh);
@@ -46,13 +45,12 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
       double d[1] = {v.x * v.x + v.y * v.y};
       tr.template add<j>(d);
     });
-    if (!g.template exchange<1>(tr.top, g0)) return;
+    if (!g.template exchange<1>(tr.top, g0, P)) return;
   }
   fin_setup_gamma(st, a.hist, g0[0]);
   uniform(st);
   for (int64_t i = 0; st.status == DS_RUNNING && i < a.maxit; ++i) {
     {  // s = A p^ ; alpha
-      g.halo(P);
       typename R::template Tree<1> tr(sh);
       g.product(P, [&](auto jc, D2 v) {
         constexpr int j = decltype(jc)::value;
@@ -61,7 +59,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
         tr.template add<j>(d);
       });
       double g1[1];
-      if (!g.template exchange<1>(tr.top, g1)) return;
+      if (!g.template exchange<1>(tr.top, g1, -1)) return;
       fin_bicg_alpha(st, g1[0]);
       uniform(st);
       if (st.status != DS_RUNNING) break;
@@ -80,8 +78,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
           g.put(Q, j, v);
         }
       }
-      if (!g.barrier()) return;
-      g.halo(Q);
+      if (!g.barrier(Q)) return;
       typename R::template Tree<2> tr(sh);
       g.product(Q, [&](auto jc, D2 v) {
         constexpr int j = decltype(jc)::value;
@@ -92,7 +89,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
         double d[2] = {qj.x * v.x + qj.y * v.y, v.x * v.x + v.y * v.y};
         tr.template add<j>(d);
       });
-      if (!g.template exchange<2>(tr.top, g2)) return;
+      if (!g.template exchange<2>(tr.top, g2, -1)) return;
     }
     const bool yz = uniform((int32_t)fin_omega(st, a.hist, g2[0], g2[1])) != 0;
     uniform(st);
@@ -116,7 +113,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
         double d[2] = {r0[j].x * r[j].x + r0[j].y * r[j].y, r[j].x * r[j].x + r[j].y * r[j].y};
         tr.template add<j>(d);
       });
-      if (!g.template exchange<2>(tr.top, g2)) return;
+      if (!g.template exchange<2>(tr.top, g2, -1)) return;
     }
     fin_bicg_beta(st, a.hist, g2[0], g2[1]);
     uniform(st);
@@ -136,7 +133,7 @@ __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResAr
         g.put(P, j, pn);
       }
     }
-    if (!g.barrier()) return;
+    if (!g.barrier(P)) return;
   }
   g.finish(x, st);
 }
@@ -160,7 +157,7 @@ __global__ __launch_bounds__(kResT) void kb_res_bicg(const ResSys<ND>* __restric
 }  // namespace
 
 hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
-  return res_dispatch(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
+  return res_dispatch<false>(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
     constexpr int K = decltype(k)::value, ND = decltype(nd)::value;
     return res_go<ND>(&k_res_bicg<K, ND, decltype(far)::value, decltype(uni)::value, decltype(pc)::value>, K, p, op, j,
                       s);

@@ -12,8 +12,7 @@ namespace {
 template <class R, class F>
 __device__ __forceinline__ bool res_residual(R& g, typename R::X& x, int w, F&& f) {
   g.load_x0(x, w);
-  if (!g.barrier()) return false;
-  g.halo(w);
+  if (!g.barrier(w)) return false;
   g.product(w, [&](auto jc, D2 ax) {
     constexpr int j = decltype(jc)::value;
     f(jc, g.get(g.a.b, j) - ax);
@@ -26,7 +25,7 @@ __device__ __forceinline__ bool res_residual(R& g, typename R::X& x, int w, F&& 
 // Window 0 holds p.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
-  using R = Res<K, ND, FAR, UNI, PC>;
+  using R = Res<K, ND, FAR, UNI, PC, true>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
@@ -53,7 +52,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
           tr.template add<j>(d);
         }))
       return;
-    if (!g.template exchange<2>(tr.top, g2)) return;
+    if (!g.template exchange<2>(tr.top, g2, P)) return;
   }
   {
     st.relres = 1.0;
@@ -67,7 +66,6 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
   }
   for (int64_t i = 0; st.status == DS_RUNNING && i < a.maxit; ++i) {
     {  // s = A p ; alpha
-      g.halo(P);
       typename R::template Tree<1> tr(sh);
       g.product(P, [&](auto jc, D2 v) {
         constexpr int j = decltype(jc)::value;
@@ -77,7 +75,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
         tr.template add<j>(d);
       });
       double g1[1];
-      if (!g.template exchange<1>(tr.top, g1)) return;
+      if (!g.template exchange<1>(tr.top, g1, -1)) return;
       fin_cg_alpha(st, g1[0]);
       uniform(st);
       if (st.status != DS_RUNNING) break;
@@ -93,7 +91,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
         double d[2] = {r[j].x * u.x + r[j].y * u.y, r[j].x * r[j].x + r[j].y * r[j].y};
         tr.template add<j>(d);
       });
-      if (!g.template exchange<2>(tr.top, g2)) return;
+      if (!g.template exchange<2>(tr.top, g2, -1)) return;
       fin_cg_beta(st, a.hist, g2);
       uniform(st);
       if (st.status != DS_RUNNING) break;
@@ -102,7 +100,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
     g.next(P);
 #pragma unroll
     for (int j = 0; j < KP; ++j) g.put(P, j, pre(j, r[j]) + beta * g.own(P, j));
-    if (!g.barrier()) return;
+    if (!g.barrier(P)) return;
   }
   g.finish(x, st);
 }
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(kResT) void k_res_cg(ResOpT<ND> op, ResArgs a) {
 // Per row in registers: r, p, s, w and x.  Window 0 holds u.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
-  using R = Res<K, ND, FAR, UNI, PC>;
+  using R = Res<K, ND, FAR, UNI, PC, true>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
@@ -134,10 +132,9 @@ __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
         g.put(U, j, pre(j, v));
       }))
     return;
-  if (!g.barrier()) return;
+  if (!g.barrier(U)) return;
   double g3[3];
   auto wsum = [&]() -> bool {  // w = A u with its three sums
-    g.halo(U);
     typename R::template Tree<3> tr(sh);
     g.product(U, [&](auto jc, D2 v) {
       constexpr int j = decltype(jc)::value;
@@ -146,7 +143,7 @@ __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
       double d[3] = {r[j].x * u.x + r[j].y * u.y, v.x * u.x + v.y * u.y, r[j].x * r[j].x + r[j].y * r[j].y};
       tr.template add<j>(d);
     });
-    return g.template exchange<3>(tr.top, g3);
+    return g.template exchange<3>(tr.top, g3, -1);
   };
   if (!wsum()) return;
   int64_t i = 0;
@@ -166,7 +163,7 @@ __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
       r[j] = r[j] - alpha * s[j];
       g.put(U, j, pre(j, r[j]));
     }
-    if (!g.barrier()) return;
+    if (!g.barrier(U)) return;
     if (!wsum()) return;
   }
   if (st.status == DS_RUNNING && i == a.maxit) {
@@ -181,7 +178,7 @@ __global__ __launch_bounds__(kResT) void k_res_cgcg(ResOpT<ND> op, ResArgs a) {
 // registers: r, p, s, z and x, with Jacobi also w, q and u.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
-  using R = Res<K, ND, FAR, UNI, PC>;
+  using R = Res<K, ND, FAR, UNI, PC, true>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
@@ -208,10 +205,9 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
         }
       }))
     return;
-  if (!g.barrier()) return;
+  if (!g.barrier(1)) return;
   double g3[3];
   {
-    g.halo(1);
     g.next(0);
     typename R::template Tree<3> tr(sh);
     g.product(1, [&](auto jc, D2 v) {
@@ -228,7 +224,7 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
       double d[3] = {r[j].x * uj.x + r[j].y * uj.y, v.x * uj.x + v.y * uj.y, r[j].x * r[j].x + r[j].y * r[j].y};
       tr.template add<j>(d);
     });
-    if (!g.template exchange<3>(tr.top, g3)) return;
+    if (!g.template exchange<3>(tr.top, g3, 0)) return;
   }
   int64_t i = 0;
   for (; i < a.maxit; ++i) {
@@ -239,7 +235,6 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
     st.iters += 1;  // the x update below
     const double alpha = st.alpha, beta = st.beta;
     const int cur = (int)(i & 1), nxt = cur ^ 1;
-    g.halo(cur);
     g.next(nxt);
     typename R::template Tree<3> tr(sh);
     g.product(cur, [&](auto jc, D2 nv) {
@@ -271,7 +266,7 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
       double d[3] = {r[j].x * uj.x + r[j].y * uj.y, wn.x * uj.x + wn.y * uj.y, r[j].x * r[j].x + r[j].y * r[j].y};
       tr.template add<j>(d);
     });
-    if (!g.template exchange<3>(tr.top, g3)) return;
+    if (!g.template exchange<3>(tr.top, g3, nxt)) return;
   }
   if (st.status == DS_RUNNING && i == a.maxit) {
     if (i == 0) fin_cgs_first(st, a.hist, g3);
@@ -283,14 +278,17 @@ __global__ __launch_bounds__(kResT) void k_res_pcg(ResOpT<ND> op, ResArgs a) {
 }  // namespace
 
 hipError_t res_launch_cg(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
-  return res_dispatch(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
+  if (j.variant == PBCGS_PIPE_CG)
+    return res_dispatch<false>(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
+      constexpr int K = decltype(k)::value, ND = decltype(nd)::value;
+      constexpr bool F = decltype(far)::value, U = decltype(uni)::value, C = decltype(pc)::value;
+      return res_go<ND>(&k_res_pcg<K, ND, F, U, C>, K, p, op, j, s);
+    });
+  return res_dispatch<true>(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
     constexpr int K = decltype(k)::value, ND = decltype(nd)::value;
     constexpr bool F = decltype(far)::value, U = decltype(uni)::value, C = decltype(pc)::value;
-    switch (j.variant) {
-      case PBCGS_CG: return res_go<ND>(&k_res_cg<K, ND, F, U, C>, K, p, op, j, s);
-      case PBCGS_CGCG: return res_go<ND>(&k_res_cgcg<K, ND, F, U, C>, K, p, op, j, s);
-      default: return res_go<ND>(&k_res_pcg<K, ND, F, U, C>, K, p, op, j, s);
-    }
+    if (j.variant == PBCGS_CG) return res_go<ND>(&k_res_cg<K, ND, F, U, C>, K, p, op, j, s);
+    return res_go<ND>(&k_res_cgcg<K, ND, F, U, C>, K, p, op, j, s);
   });
 }
 

@@ -21,7 +21,7 @@ __device__ __forceinline__ bool res_rr_due(const ResArgs& a, int64_t i) {
 // see the table of resident sizes at res_plan.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
-  using R = Res<K, ND, FAR, UNI, PC>;
+  using R = Res<K, ND, FAR, UNI, PC, false>;
   constexpr int KP = R::KP;
   extern __shared__ __align__(16) double sm[];
   __shared__ typename R::Shared sh;
@@ -37,8 +37,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
   double g5[5];
   g.load_x0(x, W);
   r0.v = 4;
-  if (!g.barrier()) return;
-  g.halo(W);
+  if (!g.barrier(W)) return;
   {
     typename R::template Tree<1> tr(sh);
     g.product(W, [&](auto jc, D2 ax) {
@@ -58,13 +57,12 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
       else g.put(W, j, r[j]);
     }
     double tot[1];
-    if (!g.template exchange<1>(tr.top, tot)) return;
+    if (!g.template exchange<1>(tr.top, tot, W)) return;
     fin_setup_gamma(st, a.hist, tot[0]);
     uniform(st);
   }
   double g1[1] = {0.0};
   if (st.status == DS_RUNNING) {  // w_0 = A r^_0
-    g.halo(W);
     typename R::template Tree<1> tr(sh);
     g.product(W, [&](auto jc, D2 y) {
       constexpr int j = decltype(jc)::value;
@@ -91,7 +89,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
         g.put(W, j, wn);
       }
     }
-    if (!g.template exchange<1>(tr.top, g1)) return;
+    if (!g.template exchange<1>(tr.top, g1, W)) return;
   }
 
   int64_t i = 0;
@@ -115,9 +113,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
           else ph[j] = r[j] + beta * (ph[j] - omega * s[j]);
           g.put(Z, j, ph[j]);
         }
-        if (!g.barrier()) return;
-        g.halo(W);
-        g.halo(Z);
+        if (!g.barrier(Z)) return;
         g.product(W, [&](auto jc, D2 y) { tv[decltype(jc)::value] = y; });  // t = A w^
         g.product(Z, [&](auto jc, D2 y) { s[decltype(jc)::value] = y; });
         __syncthreads();
@@ -131,8 +127,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
             g.put(Z, j, s[j]);
           }
         }
-        if (!g.barrier()) return;
-        g.halo(Z);
+        if (!g.barrier(Z)) return;
         D2 zn[R::kStash ? 1 : KP];
         g.product(Z, [&](auto jc, D2 y) {
           constexpr int j = decltype(jc)::value;
@@ -164,7 +159,6 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
           }
         }
       } else {
-        g.halo(W);
         g.next(Z);
         g.product(W, [&](auto jc, D2 tj) {
           constexpr int j = decltype(jc)::value;
@@ -195,7 +189,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
           tr.template add<j>(d);
         });
       }
-      if (!g.template exchange<2>(tr.top, g2)) return;
+      if (!g.template exchange<2>(tr.top, g2, Z)) return;
     }
     const bool yz = uniform((int32_t)fin_omega(st, a.hist, g2[0], g2[1])) != 0;
     uniform(st);
@@ -219,8 +213,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
         g.set_x(x, j, xj);
         g.put(W, j, xj);
       }
-      if (!g.barrier()) return;
-      g.halo(W);
+      if (!g.barrier(W)) return;
       g.product(W, [&](auto jc, D2 ax) {
         constexpr int j = decltype(jc)::value;
         r[j] = g.get(a.b, j) - ax;
@@ -233,8 +226,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
         if constexpr (PC) g.put(W, j, rh[j]);
         else g.put(W, j, r[j]);
       }
-      if (!g.barrier()) return;
-      g.halo(W);
+      if (!g.barrier(W)) return;
       st.n_rr += 1;
       g.product(W, [&](auto jc, D2 y) {
         constexpr int j = decltype(jc)::value;
@@ -259,7 +251,6 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
         }
       }
     } else {
-      g.halo(Z);
       g.next(W);
       D2 xl[KP], r0l[KP];
       auto load = [&](auto jc) {
@@ -300,7 +291,7 @@ __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResAr
         tr.template add<j>(d);
       });
     }
-    if (!g.template exchange<5>(tr.top, g5)) return;
+    if (!g.template exchange<5>(tr.top, g5, W)) return;
   }
   // maxit reached: the reduction left pending
   if (st.status == DS_RUNNING && i == a.maxit) {
@@ -329,7 +320,7 @@ __global__ __launch_bounds__(kResT) void kb_res_pipe(const ResSys<ND>* __restric
 }  // namespace
 
 hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
-  return res_dispatch(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
+  return res_dispatch<false>(p, op, j, [&](auto k, auto nd, auto far, auto uni, auto pc) -> hipError_t {
     constexpr int K = decltype(k)::value, ND = decltype(nd)::value;
     return res_go<ND>(&k_res_pipe<K, ND, decltype(far)::value, decltype(uni)::value, decltype(pc)::value>, K, p, op, j,
                       s);
