@@ -33,7 +33,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_pb_c2.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1612_01395_amd", "csrc", "kernels.hpp")]  # every solver kernel
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1612_01395_amd", "csrc", f)  # every streamed solver kernel
+                  for f in ("kernels.hpp", "method.hpp")]
 
 
 def code_text(src: str) -> str:
@@ -533,7 +534,8 @@ def main():
             del As, bs, xs, rps, cols, vals
 
     progress("section: roofline of the dominant kernel")
-    # ---- roofline of the dominant kernel: one solve with per-kernel events -------
+    # ---- roofline of the dominant streamed kernel: one solve with per-kernel events (the
+    # measured solves run in the resident form, one launch each, where it applies) -------
     _, pinfo = solver.solve(A, b, variant="pbicgstab_rr", precond="jacobi_folded", out=xbuf, time_kernels=True,
                             **common)
     ba, bb, _ = algorithmic_bytes(N, nnz, "pbicgstab", False, index_bytes=ib, dia=nd, codes=pinfo.value_codes)
@@ -545,6 +547,7 @@ def main():
     grid_threads = -(-N // (256 * tune["best"])) * 256
     roofline = {
         "bound": "hbm",
+        "scope": "streamed kernels, in a solve of their own with per-kernel events",
         "kernel": ("k_pa (t = A w, recurrences, (q,y),(y,y))", "k_pb (v = A z, x/r/w updates, 5 dots)")[dom],
         "achieved": round(achieved, 1),
         "peak": HBM_PEAK_GBS,

@@ -157,14 +157,17 @@ typedef struct {
     int32_t kernel_calls[2]; /* launches timed for kernel_ms                              */
     int32_t rows_per_wave_blocks; /* the launch shape that ran: 64-row blocks per wave,  */
     int32_t workgroups;           /* and workgroups of 256 threads (the system's own in a
-                                     batch)                                               */
+                                     batch); of a solve in the resident form, the shape of
+                                     the launches around it                               */
     int32_t value_codes;          /* 1 when the solve read its diagonal layout's values
                                      (binary64, or binary32 and binary64 for the
                                      precision form) as one-byte codes into a table of
                                      each diagonal's distinct values (value indexing, used
                                      for layouts of at most 8 diagonals none of which
                                      holds more than 16 distinct values, from 2^18 rows,
-                                     without a Jacobi vector; same results)             */
+                                     without a Jacobi vector; same results), or, in the
+                                     resident form, as one constant per diagonal under
+                                     the same conditions                                 */
 } pbcgs_info;
 
 /* Create a context on HIP device `device` working on stream `hip_stream`
@@ -334,6 +337,19 @@ int pbcgs_jacobi_dinv(pbcgs_ctx_t ctx, pbcgs_op_t A, double* dinv);
  * caller's A and the returned x.  opts and info are host structs.  The call
  * enqueues on the context's stream and returns after the solve has finished;
  * the host reads the 64-byte device status once every check_every iterations.
+ *
+ * Resident form: a binary64 solve of at most 2^21 rows whose operator has at
+ * most 7 diagonals (a CSR operator's diagonal layout, or a constant 5- or
+ * 7-point stencil) runs, for every variant but CA-BiCGStab, as one cooperative
+ * launch that keeps the Krylov vectors in registers and LDS; p-BiCGStab and
+ * BiCGStab with Jacobi as written and p-CG with Jacobi up to 2^20 rows, and
+ * diagonals whose values vary up to 2^18 rows.  Same results, bit for bit.
+ * opts.flags bits 0, 1, 3 and 4, the perturbation hook and the allocation-free
+ * entry point keep the streamed kernels, and so does a launch that the device
+ * refuses or that finds the device busy for about a second (the solve then
+ * starts again from x_0, which the resident launch does not touch).
+ * Streamed solves of more than 2^21 rows (binary64 p-BiCGStab: 2^22) launch
+ * workgroups of 1,024 rows whatever shape was tuned.
  */
 int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const double* dinv,
                 const pbcgs_opts* opts, pbcgs_info* info);

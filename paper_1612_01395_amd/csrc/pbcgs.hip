@@ -572,8 +572,8 @@ int true_relres(pbcgs_ctx_t ctx, const Op& op, const Args& a0, double rho0, doub
 // Per-(operator, preconditioner) driver.
 // ---------------------------------------------------------------------------
 constexpr int32_t kManyRows = 1 << 21;  // see Driver::take_many
-constexpr int kManyR = 8;
-constexpr int kFirstChunk = 8;  // iterations of a solve's first two chunks
+constexpr int kManyR = 4;
+constexpr int kFirstChunk = 8;  // iterations of a CSR-stream solve's first two chunks
 // MP: precision form (Op is the binary32 operator, Op64 the binary64 one).
 template <class Op, int PC, class Op64 = Op, bool MP = false>
 struct Driver {
@@ -666,10 +666,16 @@ struct Driver {
   // a line or a plane away come round after more bytes than the caches hold
   // and the gathered vector is fetched several times; small workgroups,
   // dispatched in order, sweep the system as one window.  Each kernel's sums
-  // are folded by one small kernel before they are consumed.
+  // are folded by one small kernel before they are consumed.  60 iterations
+  // with 1,024 workgroups / R = 4 / R = 8 (ms): 7-point p-BiCGStab 165^3 17.6 /
+  // 12.7 / 13.7, 200^3 24.9 / 21.9 / 24.4, BiCGStab 170^3 16.1 / 12.5 / 13.1,
+  // binary32 130^3 5.5 / 4.8 / 4.8, matrix-free 180^3 32.0 / 27.1 / 28.1.  Where
+  // the XCD-contiguous indices are on (binary64 p-BiCGStab up to 2^22 rows) they
+  // do as well (145^3 8.1 / 8.4 / 8.9) and are kept.
   bool take_many() {
     const int mode = env_int("PBCGS_MANY", -1);
-    if (mode == 0 || ctx->noalloc || ctx->streamed_only || (mode < 0 && a.n <= kManyRows)) return false;
+    if (mode == 0 || ctx->noalloc || ctx->streamed_only || (mode < 0 && a.n <= (a.wg == -2 ? 2 : 1) * kManyRows))
+      return false;
     if (std::getenv("PBCGS_R") || std::getenv("PBCGS_GTARGET")) return false;
     const int R = mode > 0 ? mode : kManyR;
     const int64_t G = ((int64_t)a.n + 256 * (int64_t)R - 1) / (256 * (int64_t)R);
@@ -1085,8 +1091,11 @@ struct Driver {
       for (;;) {
         while (!stop && launched < o.maxit && npend < 2) {
           int m = (int)std::min<int64_t>(check, o.maxit - launched);
-          // the first polls come early: a solve of 20 iterations is not given 64
-          if (o.check_every <= 0 && launched < 2 * kFirstChunk) m = std::min(m, kFirstChunk);
+          // The first polls of a CSR-stream solve come early: matrices without
+          // diagonals tend to need tens of iterations, and one that needs 16 was
+          // given 64 (200,003 rows, 0.9 -> 0.73 ms).  Elsewhere the two more
+          // chunk boundaries cost more than they save (27-point 50^3 3.5 %).
+          if (IsCsr<Op>::value && o.check_every <= 0 && launched < 2 * kFirstChunk) m = std::min(m, kFirstChunk);
           if (rate < 0.0 && o.tol > 0.0 && last_rel > 0.0) {
             const double need = (std::log(o.tol) - std::log(last_rel)) / rate;  // from the last poll
             const int64_t ahead = launched - last_it;                           // queued since then

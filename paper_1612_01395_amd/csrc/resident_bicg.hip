@@ -10,7 +10,8 @@ namespace {
 // Five exchanges per iteration, two of them barriers only (q^ and p^ have to
 // reach the other workgroups before their products).  Per row in registers:
 // r0, r, s, y and x, with Jacobi also p and q.  Window 0 holds p^ (p), window
-// 1 q^ (q).
+// 1 q^ (q).  Bound by its five exchanges; measured per iteration, streamed
+// kernels / this one: 41^3 26.8 / 13.8 us, 64^3 27.7 / 16.4, 128^3 80.4 / 40.7.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __device__ __forceinline__ void res_bicg_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
   using R = Res<K, ND, FAR, UNI, PC, true>;

@@ -16,9 +16,12 @@ __device__ __forceinline__ bool res_rr_due(const ResArgs& a, int64_t i) {
 }
 
 // Per row in registers: r, s, p^, t / v (one slot: t is dead when v is made), x
-// and r0 (the last two in memory for K = 16), with Jacobi also w, z, r^, s^.  Window
-// 0 holds w^ (w), window 1 z^ (z).  Measured on one system (folded Jacobi):
-// see the table of resident sizes at res_plan.
+// and r0 (the last two in memory for K = 16), with Jacobi also w, z, r^, s^.
+// Window 0 holds w^ (w), window 1 z^ (z).  Two exchanges per iteration.  Bound
+// by the exchange on small systems and by the vector ALUs (about 300
+// instructions a pair and phase) and the far reads on large ones; measured per
+// iteration, streamed kernels / this one: 64^2 14.6 / 6.8 us, 64^3 21.6 / 11,
+// 100^3 47.9 / 23, 128^3 (folded Jacobi) 76.6 / 42.
 template <int K, int ND, bool FAR, bool UNI, bool PC>
 __device__ __forceinline__ void res_pipe_solve(const ResOpT<ND>& op, const ResArgs& a, int wg) {
   using R = Res<K, ND, FAR, UNI, PC, false>;

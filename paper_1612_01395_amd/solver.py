@@ -294,7 +294,7 @@ class SolveInfo:
     kernel_ms: tuple
     kernel_calls: tuple
     history: torch.Tensor | None = None
-    shape: tuple = (0, 0)  # the launch shape that ran: (64-row blocks per wave, workgroups)
+    shape: tuple = (0, 0)  # the launch shape: (64-row blocks per wave, workgroups); around a resident launch
     value_codes: bool = False  # the layout's values were read as codes into per-diagonal tables
 
     @property
