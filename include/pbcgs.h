@@ -168,6 +168,9 @@ typedef struct {
                                      without a Jacobi vector; same results), or, in the
                                      resident form, as one constant per diagonal under
                                      the same conditions                                 */
+    int32_t resident_rows;        /* rows per thread of a solve that ran in the resident
+                                     form (see pbcgs_solve); 0: it ran in the streamed
+                                     kernels                                             */
 } pbcgs_info;
 
 /* Create a context on HIP device `device` working on stream `hip_stream`

@@ -58,6 +58,7 @@ class Info(ctypes.Structure):
         ("rows_per_wave_blocks", ctypes.c_int32),
         ("workgroups", ctypes.c_int32),
         ("value_codes", ctypes.c_int32),
+        ("resident_rows", ctypes.c_int32),
     ]
 
 

@@ -1331,6 +1331,7 @@ int run_resident(pbcgs_ctx_t ctx, const ResPlan& plan, const ResOp& op, const Ar
   info->ms = ms;
   info->rows_per_wave_blocks = a.R;  // of the launches around it
   info->workgroups = a.G;
+  info->resident_rows = plan.K;
   *rho0 = fin.rho0;
   *done = true;
   return PBCGS_SUCCESS;
@@ -1751,6 +1752,7 @@ struct BatchDriver {
       const double nr = util[(size_t)k * 4 + 3].result;
       in.relres_true = (d.rho0 > 0.0) ? std::sqrt(nr) / d.rho0 : 0.0;
       in.ms = ms;
+      in.resident_rows = done ? kResBatchK : 0;
       worst = std::max(worst, in.status);
     }
     return worst;

@@ -92,6 +92,7 @@ struct ResBatchSys {  // what the caller knows of a system
   DevState* st;
 };
 constexpr int kResBatchVecs = 4;    // three exchange buffers and x
+constexpr int kResBatchK = 8;       // rows per thread
 
 // Launches of a batch: each a list of systems with their first workgroup.
 struct ResBatchPlan {

@@ -54,7 +54,6 @@ typedef unsigned U4 __attribute__((ext_vector_type(4)));
 constexpr int kResSpin = 1 << 19;  // polls before a wait gives up (about a second)
 constexpr int kResFront = 2;       // doubles before row 0 in an exchange buffer
 constexpr int kSc1 = 16;           // buffer cache policy: agent scope
-constexpr int kResBatchK = 8;      // rows per thread of batched launches
 
 template <int ND>
 struct ResOpT {

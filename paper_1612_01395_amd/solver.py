@@ -295,7 +295,9 @@ class SolveInfo:
     kernel_calls: tuple
     history: torch.Tensor | None = None
     shape: tuple = (0, 0)  # the launch shape: (64-row blocks per wave, workgroups); around a resident launch
-    value_codes: bool = False  # the layout's values were read as codes into per-diagonal tables
+    value_codes: bool = False  # the layout's values were read as codes into per-diagonal tables, or
+    #                            (resident form, from 2^18 rows) as one constant per diagonal
+    resident_rows: int = 0  # rows per thread of the resident form; 0: the streamed kernels ran
 
     @property
     def status_name(self) -> str:
@@ -387,6 +389,7 @@ def _solve(entry, A: Operator, b: torch.Tensor, x0, *, variant, precond, dinv, t
                    info.ms, tuple(info.kernel_ms), tuple(info.kernel_calls))
     si.shape = (int(info.rows_per_wave_blocks), int(info.workgroups))
     si.value_codes = bool(info.value_codes)
+    si.resident_rows = int(info.resident_rows)
     if hist is not None:
         si.history = hist[: info.iters + 1]
     return x, si
@@ -447,7 +450,8 @@ def solve_batched(ops: list, bs: list, x0s: list | None = None, *, variant: str 
     infos = (L.Info * nsys)()
     L.check(L.lib().pbcgs_solve_batched(ctx.handle, nsys, hs, bp, xp, ctypes.byref(o), infos), ctx.handle)
     out = [SolveInfo(i.iters, i.n_rr, i.status, i.syncs_per_iter, i.relres_rec, i.relres_true, i.ms,
-                     tuple(i.kernel_ms), tuple(i.kernel_calls), shape=(int(i.rows_per_wave_blocks), int(i.workgroups)))
+                     tuple(i.kernel_ms), tuple(i.kernel_calls), shape=(int(i.rows_per_wave_blocks), int(i.workgroups)),
+                     resident_rows=int(i.resident_rows))
            for i in infos]
     return xs, out
 
