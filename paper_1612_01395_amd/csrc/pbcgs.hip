@@ -97,7 +97,7 @@ struct pbcgs_ctx_s {
   int coop = -1;            // device supports cooperative launches (-1: not asked yet)
   double* bigpart = nullptr;     // partial sums of launches of more than kMaxG workgroups
   size_t bigpart_cap = 0;        // doubles
-  unsigned char* bres = nullptr;  // batched resident solves: tables and vectors
+  unsigned char* bres = nullptr;  // batched resident solves: tables
   size_t bres_cap = 0;            // bytes
   bool streamed_only = false;     // the autotuners time the streamed kernels
   unsigned char* res = nullptr;  // resident solves: exchange words, then kResAux bytes
@@ -1486,6 +1486,29 @@ int grow(pbcgs_ctx_t ctx, T*& p, size_t& cap, size_t count, const char* what) {
   return PBCGS_SUCCESS;
 }
 
+// The resident form of a whole batch (resident.hpp); *done = false, with
+// nothing of the caller's written, when it did not run to its end.
+int run_resident_batch(pbcgs_ctx_t ctx, const pbcgs_opts& o, const ResBatchPlan& plan,
+                       const std::vector<ResBatchSys>& sys, bool* done) {
+  hipStream_t s = ctx->stream;
+  *done = false;
+  int32_t* err = nullptr;
+  HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
+  if (res_batch_launch(plan, sys, resident_job(o), ctx->bres, s, &err) != hipSuccess) {
+    (void)hipGetLastError();
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    return PBCGS_SUCCESS;
+  }
+  HIP_TRY(ctx, hipMemcpyAsync(ctx->hflag, err, sizeof *err, hipMemcpyDeviceToHost, s));
+  HIP_TRY(ctx, hipStreamSynchronize(s));
+  if (*ctx->hflag != 0) return PBCGS_SUCCESS;
+  for (const ResBatchSys& y : sys)
+    HIP_TRY(ctx, hipMemcpyAsync(const_cast<double*>(y.x0), y.vecs + 3 * y.stride, sizeof(double) * (size_t)y.op.n,
+                                hipMemcpyDeviceToDevice, s));
+  *done = true;
+  return PBCGS_SUCCESS;
+}
+
 // Batched solve of independent CSR systems without a preconditioner: the
 // schedule of Driver, every launch covering all systems (see SysDesc).
 // Op: CsrOp (int32 columns), CsrOp16 (every system holds compact columns) or
@@ -1507,35 +1530,6 @@ struct BatchDriver {
     std::memset(&tmpl, 0, sizeof tmpl);
     tmpl.pstride = tg;
     tmpl.aform = alpha_form(o_);
-  }
-
-  // The resident form of the whole batch (resident.hpp); set by the caller
-  // when every system fits it.
-  const ResBatchPlan* res_plan_ = nullptr;
-  const std::vector<ResBatchSys>* res_sys = nullptr;
-
-  // Runs it; *done = false, with nothing of the caller's written, when it did
-  // not run to its end.
-  int run_resident(bool* done) {
-    hipStream_t s = ctx->stream;
-    *done = false;
-    int32_t* err = nullptr;
-    int32_t bad = 1;
-    if (res_batch_launch(*res_plan_, *res_sys, resident_job(o), ctx->bres, s, &err) != hipSuccess) {
-      (void)hipGetLastError();
-      HIP_TRY(ctx, hipStreamSynchronize(s));
-      return PBCGS_SUCCESS;
-    }
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->hflag, err, sizeof bad, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (*ctx->hflag != 0) return PBCGS_SUCCESS;
-    for (int32_t k = 0; k < nsys; ++k) {
-      const ResBatchSys& y = (*res_sys)[(size_t)k];
-      HIP_TRY(ctx, hipMemcpyAsync(const_cast<double*>(y.x0), y.vecs + 3 * y.stride, sizeof(double) * (size_t)y.op.n,
-                                  hipMemcpyDeviceToDevice, s));
-    }
-    *done = true;
-    return PBCGS_SUCCESS;
   }
 
   double* part(int which) const { return ctx->bpart + (size_t)which * kMaxD * totalG; }
@@ -1703,19 +1697,17 @@ struct BatchDriver {
     return PBCGS_SUCCESS;
   }
 
-  int run(pbcgs_info* infos) {
+  // resident: run_resident_batch() has done the iterations, and only the true
+  // residuals and the reports are left.
+  int run(pbcgs_info* infos, bool resident) {
     hipStream_t s = ctx->stream;
     const bool use_graph = !(o.flags & 1);
     const int check = o.check_every > 0 ? o.check_every : 8;
     const size_t nst = (size_t)nsys * 4;
-    HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
-    bool done = false;
-    if (res_plan_) {
+    if (resident) {
       q = 0;  // the final states are in slot 0
-      const int rc = run_resident(&done);
-      if (rc != PBCGS_SUCCESS) return rc;
-    }
-    if (!done) {
+    } else {
+      HIP_TRY(ctx, hipEventRecord(ctx->ev_start, s));
       const int rc = run_streamed(use_graph, check, nst);
       if (rc != PBCGS_SUCCESS) return rc;
     }
@@ -1752,7 +1744,7 @@ struct BatchDriver {
       const double nr = util[(size_t)k * 4 + 3].result;
       in.relres_true = (d.rho0 > 0.0) ? std::sqrt(nr) / d.rho0 : 0.0;
       in.ms = ms;
-      in.resident_rows = done ? kResBatchK : 0;
+      in.resident_rows = resident ? kResBatchK : 0;
       worst = std::max(worst, in.status);
     }
     return worst;
@@ -2919,12 +2911,10 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
   if (rc == PBCGS_SUCCESS) rc = grow(ctx, ctx->bws, ctx->bws_cap, wsneed, "batch vectors");
   if (rc == PBCGS_SUCCESS) rc = grow(ctx, ctx->bst, ctx->bst_cap, nst, "batch states");
   if (rc == PBCGS_SUCCESS) rc = grow(ctx, ctx->bpart, ctx->bpart_cap, (size_t)PB_COUNT * kMaxD * totalG, "partials");
-  if (rc == PBCGS_SUCCESS && dia) rc = grow(ctx, ctx->bdia, ctx->bdia_cap, dianeed, "diagonal-layout values");
   if (rc != PBCGS_SUCCESS) return rc;
   PoisonScope poison_scope(ctx, (o.flags & 32) != 0);
   poison(ctx, ctx->bws, wsneed * sizeof(double));
   poison(ctx, ctx->bpart, (size_t)PB_COUNT * kMaxD * (size_t)totalG * sizeof(double));
-  if (dia) poison(ctx, ctx->bdia, dianeed * sizeof(double));
   if (ctx->bhst_cap < nst) {
     if (ctx->bhst) { (void)hipStreamSynchronize(ctx->stream); (void)hipHostFree(ctx->bhst); ctx->bhst = nullptr; }
     ctx->bhst_cap = 0;
@@ -2935,27 +2925,27 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
     ctx->bhst_cap = nst;
   }
   std::vector<int32_t> map((size_t)totalG);
-  size_t off = 0, doff = 0;
+  size_t off = 0;
   for (int32_t k = 0; k < nsys; ++k) {
     SysDesc& d = desc[(size_t)k];
     d.ws = ctx->bws + off;
     off += (size_t)8 * (size_t)d.np;
-    if (dia) {
-      d.dva = ctx->bdia + doff;
-      doff += (size_t)d.nd * (size_t)d.np;
-    }
     d.st = ctx->bst + (size_t)k * 4;
     for (int32_t g = 0; g < d.G; ++g) map[(size_t)d.wg0 + g] = k;
   }
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->bsys, desc.data(), desc.size() * sizeof(SysDesc), hipMemcpyHostToDevice, ctx->stream));
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->bmap, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host tables may go away after this
-  // Every system within the resident form: the batch runs in it, and only the
-  // true residuals are left to the launches over the whole batch.
-  std::vector<ResBatchSys> rsys;
-  ResBatchPlan rplan;
+  auto upload = [&]() -> int {
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->bsys, desc.data(), desc.size() * sizeof(SysDesc), hipMemcpyHostToDevice, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->bmap, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host tables may change or go away after this
+    return PBCGS_SUCCESS;
+  };
+  // Every system within the resident form: the batch runs in it, on the
+  // streamed solve's vectors, and only the true residuals are left to the
+  // launches over the whole batch.  Whatever it cannot have (memory for its
+  // tables, a launch) leaves the batch to the streamed kernels.
+  bool resident = false;
   if (dia && resident_options(ctx, o)) {
-    size_t vecs = 0;
+    std::vector<ResBatchSys> rsys;
     for (int32_t k = 0; k < nsys; ++k) {
       ResBatchSys y;
       std::memset(&y, 0, sizeof y);
@@ -2965,37 +2955,45 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
       y.va = A[k]->va;
       y.b = b[k];
       y.x0 = x[k];
-      y.stride = (int64_t)padded(A[k]->n) + (int64_t)kResVecPad;
-      y.st = ctx->bst + (size_t)k * 4;
-      vecs += (size_t)kResBatchVecs * (size_t)y.stride;
+      y.vecs = desc[(size_t)k].ws;
+      y.stride = desc[(size_t)k].np + (int64_t)kResVecPad;
+      static_assert(kResBatchVecs * (64 + kResVecPad) <= 8 * 64, "they fit the eight workspace vectors (np >= 64)");
+      y.st = desc[(size_t)k].st;
       rsys.push_back(y);
     }
-    rplan = res_batch_plan(rsys, ctx->cus);
-    if (rplan.ok) {
-      const size_t tables = (res_batch_bytes(rplan, nsys) + 255) & ~(size_t)255;
-      rc = grow(ctx, ctx->bres, ctx->bres_cap, tables + vecs * sizeof(double), "resident batch");
+    ResBatchPlan plan = res_batch_plan(rsys, ctx->cus);
+    if (plan.ok && grow(ctx, ctx->bres, ctx->bres_cap, res_batch_bytes(plan), "resident batch") != PBCGS_SUCCESS) {
+      (void)hipGetLastError();
+      plan.ok = false;
+    }
+    bool uniform = false;
+    if (plan.ok && res_batch_uniform(rsys, ctx->bres, ctx->stream, &uniform) != hipSuccess) {
+      (void)hipGetLastError();
+      uniform = false;
+    }
+    if (plan.ok && uniform) {
+      rc = upload();
+      if (rc == PBCGS_SUCCESS) rc = run_resident_batch(ctx, o, plan, rsys, &resident);
       if (rc != PBCGS_SUCCESS) return rc;
-      double* v = reinterpret_cast<double*>(ctx->bres + tables);
-      poison(ctx, v, vecs * sizeof(double));
-      for (ResBatchSys& y : rsys) {
-        y.vecs = v;
-        v += kResBatchVecs * y.stride;
-      }
-      bool uniform = false;
-      HIP_TRY(ctx, res_batch_uniform(rsys, ctx->bres, ctx->stream, &uniform));
-      rplan.ok = uniform;
     }
   }
-  auto run = [&](auto driver) -> int {
-    if (rplan.ok) {
-      driver.res_plan_ = &rplan;
-      driver.res_sys = &rsys;
+  if (!resident) {
+    if (dia) {
+      rc = grow(ctx, ctx->bdia, ctx->bdia_cap, dianeed, "diagonal-layout values");
+      if (rc != PBCGS_SUCCESS) return rc;
+      poison(ctx, ctx->bdia, dianeed * sizeof(double));
+      size_t doff = 0;
+      for (SysDesc& d : desc) {
+        d.dva = ctx->bdia + doff;
+        doff += (size_t)d.nd * (size_t)d.np;
+      }
     }
-    return driver.run(infos);
-  };
-  const int st = dia && !rplan.ok ? run(BatchDriver<DiaOpB>(ctx, o, nsys, (int32_t)totalG))
-                 : compact        ? run(BatchDriver<CsrOp16>(ctx, o, nsys, (int32_t)totalG))
-                                  : run(BatchDriver<CsrOp>(ctx, o, nsys, (int32_t)totalG));
+    rc = upload();
+    if (rc != PBCGS_SUCCESS) return rc;
+  }
+  const int st = dia && !resident ? BatchDriver<DiaOpB>(ctx, o, nsys, (int32_t)totalG).run(infos, resident)
+                 : compact        ? BatchDriver<CsrOp16>(ctx, o, nsys, (int32_t)totalG).run(infos, resident)
+                                  : BatchDriver<CsrOp>(ctx, o, nsys, (int32_t)totalG).run(infos, resident);
   if (st >= 0)
     for (int32_t k = 0; k < nsys; ++k) {
       infos[k].rows_per_wave_blocks = desc[(size_t)k].R;

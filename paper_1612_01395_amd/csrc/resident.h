@@ -87,7 +87,7 @@ struct ResBatchSys {  // what the caller knows of a system
   const double* va;
   const double* b;
   const double* x0;
-  double* vecs;       // kResBatchVecs vectors of `stride` doubles
+  double* vecs;       // kResBatchVecs vectors of `stride` doubles, 16-byte aligned
   int64_t stride;
   DevState* st;
 };
@@ -104,7 +104,7 @@ struct ResBatchPlan {
 ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus);
 
 // Device bytes of a batch's tables (descriptors, maps, words, uniform values).
-size_t res_batch_bytes(const ResBatchPlan& p, int nsys);
+size_t res_batch_bytes(const ResBatchPlan& p);
 
 // Uploads the descriptors of res_uniform for every system, runs it and reads
 // the values into sys[k].op.c; *uniform: every system has one value per

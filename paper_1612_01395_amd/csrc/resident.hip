@@ -144,13 +144,13 @@ __device__ __forceinline__ void uniform_ref(const UniformArgs& u) {
 }
 
 // Every entry against its diagonal's reference.
-__device__ __forceinline__ void uniform_check(const UniformArgs& u) {
+__device__ __forceinline__ void uniform_check(const UniformArgs& u, int block, int blocks) {
   if (*u.flag) return;
   u64 ref[kResMaxND];
 #pragma unroll
   for (int d = 0; d < kResMaxND; ++d) ref[d] = d < u.nd ? u.ref[d] : 0;
   bool same = true;
-  for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < u.n; i += gridDim.x * 256) {
+  for (int32_t i = block * 256 + threadIdx.x; i < u.n; i += blocks * 256) {
     const uint32_t m = u.mask[i];
     int32_t k = u.rp[i];
 #pragma unroll
@@ -165,7 +165,9 @@ __device__ __forceinline__ void uniform_check(const UniformArgs& u) {
 }
 
 __global__ __launch_bounds__(1024) void k_uniform_ref(UniformArgs u) { uniform_ref(u); }
-__global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) { uniform_check(u); }
+__global__ __launch_bounds__(256) void k_uniform_check(UniformArgs u) {
+  uniform_check(u, (int)blockIdx.x, (int)gridDim.x);
+}
 
 }  // namespace
 
@@ -182,10 +184,12 @@ hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, co
 // ---- batches ----
 namespace {
 
-// Layout of a batch's tables.
+// Layout of a batch's tables: exchange words only for the `multi` systems of
+// more than one workgroup (the others exchange nothing; 10,000 of them would
+// hold 0.8 GB).
 struct BatchTables {
   size_t uni, ref, err, words, sys, map, bytes;
-  BatchTables(int nsys, int maps) {
+  BatchTables(int nsys, int maps, int multi) {
     auto take = [this](size_t b) {
       const size_t at = bytes;
       bytes += (b + 255) & ~(size_t)255;
@@ -195,20 +199,22 @@ struct BatchTables {
     uni = take(sizeof(UniformArgs) * (size_t)nsys);
     ref = take(kResAux * (size_t)nsys);
     err = take(sizeof(int32_t));
-    words = take(sizeof(u64) * (size_t)kResWords * nsys);
+    words = take(sizeof(u64) * (size_t)kResWords * multi);
     sys = take(sizeof(ResSys<7>) * (size_t)nsys);
     map = take(sizeof(int2) * (size_t)maps);
   }
 };
 
 __global__ __launch_bounds__(1024) void kb_uniform_ref(const UniformArgs* us) { uniform_ref(us[blockIdx.x]); }
-__global__ __launch_bounds__(256) void kb_uniform_check(const UniformArgs* us) { uniform_check(us[blockIdx.y]); }
+__global__ __launch_bounds__(256) void kb_uniform_check(const UniformArgs* us) {
+  uniform_check(us[blockIdx.x], (int)blockIdx.y, (int)gridDim.y);
+}
 
 template <int ND>
 __global__ __launch_bounds__(256) void kb_res_init(const ResSys<ND>* sys) {
-  const ResArgs& a = sys[blockIdx.y].a;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < kResWords) a.words[i] = 0;
+  const ResArgs& a = sys[blockIdx.x].a;
+  const int i = blockIdx.y * 256 + threadIdx.x;
+  if (a.G > 1 && i < kResWords) a.words[i] = 0;
   if (i == 0) {
     *a.err = 0;
     a.st->status = -1;
@@ -220,6 +226,7 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
                         const BatchTables& t, hipStream_t s) {
   const int nsys = (int)sys.size();
   std::vector<ResSys<ND>> h((size_t)nsys);
+  size_t multi = 0;
   for (int k = 0; k < nsys; ++k) {
     const ResBatchSys& y = sys[(size_t)k];
     ResJob j = opts;
@@ -231,7 +238,8 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
     j.x0 = y.x0;
     j.vecs = y.vecs;
     j.stride = y.stride;
-    j.words = reinterpret_cast<u64*>(base + t.words) + (size_t)k * kResWords;
+    j.words = reinterpret_cast<u64*>(base + t.words) + multi * kResWords;
+    if (p.G[(size_t)k] > 1) ++multi;
     j.err = reinterpret_cast<int32_t*>(base + t.err);
     j.st = y.st;
     ResPlan q;
@@ -255,7 +263,7 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
   if (e == hipSuccess) e = hipMemcpyAsync(dmap, map.data(), sizeof(int2) * map.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go away
   if (e != hipSuccess) return e;
-  kb_res_init<ND><<<dim3((kResWords + 255) / 256, (unsigned)nsys), 256, 0, s>>>(dsys);
+  kb_res_init<ND><<<dim3((unsigned)nsys, (kResWords + 255) / 256), 256, 0, s>>>(dsys);  // y is limited to 65,535
   for (size_t l = 0; l < p.launches.size(); ++l) {
     int W = 0, H = 0;
     for (int k : p.launches[l]) {
@@ -308,15 +316,20 @@ ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus) {
   return p;
 }
 
-size_t res_batch_bytes(const ResBatchPlan& p, int nsys) {
-  int maps = 0;
-  for (int g : p.G) maps += g;
-  return BatchTables(nsys, maps).bytes;
+static BatchTables batch_tables(const ResBatchPlan& p) {
+  int maps = 0, multi = 0;
+  for (int g : p.G) {
+    maps += g;
+    multi += g > 1 ? 1 : 0;
+  }
+  return BatchTables((int)p.G.size(), maps, multi);
 }
+
+size_t res_batch_bytes(const ResBatchPlan& p) { return batch_tables(p).bytes; }
 
 hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStream_t s, bool* uniform) {
   const int nsys = (int)sys.size();
-  const BatchTables t(nsys, 0);
+  const BatchTables t(nsys, 0, 0);  // the two tables used here come first
   char* base = static_cast<char*>(tables);
   std::vector<UniformArgs> h((size_t)nsys);
   int32_t nmax = 0;
@@ -332,7 +345,7 @@ hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStr
   hipError_t e = hipMemcpyAsync(base + t.uni, h.data(), sizeof(UniformArgs) * h.size(), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
   kb_uniform_ref<<<nsys, 1024, 0, s>>>(d);
-  kb_uniform_check<<<dim3((unsigned)std::min((nmax + 1023) / 1024, 256), (unsigned)nsys), 256, 0, s>>>(d);
+  kb_uniform_check<<<dim3((unsigned)nsys, (unsigned)std::min((nmax + 1023) / 1024, 256)), 256, 0, s>>>(d);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(out.data(), base + t.ref, out.size(), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -349,9 +362,7 @@ hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStr
 
 hipError_t res_batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, void* tables,
                             hipStream_t s, int32_t** err_word) {
-  int maps = 0;
-  for (int g : p.G) maps += g;
-  const BatchTables t((int)sys.size(), maps);
+  const BatchTables t = batch_tables(p);
   char* base = static_cast<char*>(tables);
   *err_word = reinterpret_cast<int32_t*>(base + t.err);
   if (p.nd <= 5) return batch_launch<5>(p, sys, opts, base, t, s);
