@@ -1502,9 +1502,7 @@ int run_resident_batch(pbcgs_ctx_t ctx, const pbcgs_opts& o, const ResBatchPlan&
   HIP_TRY(ctx, hipMemcpyAsync(ctx->hflag, err, sizeof *err, hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
   if (*ctx->hflag != 0) return PBCGS_SUCCESS;
-  for (const ResBatchSys& y : sys)
-    HIP_TRY(ctx, hipMemcpyAsync(const_cast<double*>(y.x0), y.vecs + 3 * y.stride, sizeof(double) * (size_t)y.op.n,
-                                hipMemcpyDeviceToDevice, s));
+  HIP_TRY(ctx, res_batch_copy_x(plan, sys, ctx->bres, s));
   *done = true;
   return PBCGS_SUCCESS;
 }
@@ -2961,7 +2959,7 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
       y.st = desc[(size_t)k].st;
       rsys.push_back(y);
     }
-    ResBatchPlan plan = res_batch_plan(rsys, ctx->cus);
+    ResBatchPlan plan = res_batch_plan(rsys, ctx->cus, env_int("PBCGS_PERSIST", -1) == 1);
     if (plan.ok && grow(ctx, ctx->bres, ctx->bres_cap, res_batch_bytes(plan), "resident batch") != PBCGS_SUCCESS) {
       (void)hipGetLastError();
       plan.ok = false;

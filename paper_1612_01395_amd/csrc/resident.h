@@ -99,9 +99,10 @@ struct ResBatchPlan {
   bool ok = false;
   int nd = 0;                       // slots: 5 or 7
   std::vector<std::vector<int>> launches;
+  std::vector<int> singles;         // systems of one workgroup left over, one ordinary launch
   std::vector<int> G, H;            // per system
 };
-ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus);
+ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus, bool any_size);
 
 // Device bytes of a batch's tables (descriptors, maps, words, uniform values).
 size_t res_batch_bytes(const ResBatchPlan& p);
@@ -115,8 +116,13 @@ hipError_t res_batch_uniform(std::vector<ResBatchSys>& sys, void* tables, hipStr
 // is nonzero afterwards when a wait timed out.  x of system k: its vecs + 3 stride.
 hipError_t res_batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, void* tables,
                             hipStream_t s, int32_t** err_word);
-hipError_t res_launch_batch_pipe(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s);
-hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s);
+// Queues the copies of every x to the caller's, after a launch without errors.
+hipError_t res_batch_copy_x(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, void* tables, hipStream_t s);
+// coop: a cooperative launch, every workgroup on the chip at once
+hipError_t res_launch_batch_pipe(int nd, const void* sys, const int2* map, int workgroups, size_t lds, bool coop,
+                                 hipStream_t s);
+hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, bool coop,
+                                 hipStream_t s);
 
 // per method: its kernels live in a translation unit of their own
 hipError_t res_launch_pipe(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s);

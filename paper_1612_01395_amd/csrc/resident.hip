@@ -222,6 +222,14 @@ __global__ __launch_bounds__(256) void kb_res_init(const ResSys<ND>* sys) {
 }
 
 template <int ND>
+__global__ __launch_bounds__(256) void kb_res_copy_x(const ResSys<ND>* sys) {
+  const ResSys<ND>& y = sys[blockIdx.x];
+  const double* v = y.a.vecs + 3 * y.a.stride;
+  double* x = const_cast<double*>(y.a.x0);
+  for (int i = blockIdx.y * 256 + threadIdx.x; i < y.op.n; i += gridDim.y * 256) x[i] = v[i];
+}
+
+template <int ND>
 hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, const ResJob& opts, char* base,
                         const BatchTables& t, hipStream_t s) {
   const int nsys = (int)sys.size();
@@ -252,11 +260,17 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
   }
   std::vector<int2> map;
   std::vector<size_t> first;
-  for (const auto& l : p.launches) {
+  auto list = [&](const std::vector<int>& l) {
     first.push_back(map.size());
     for (int k : l)
       for (int g = 0; g < p.G[(size_t)k]; ++g) map.push_back(int2{k, g});
-  }
+  };
+  for (const auto& l : p.launches) list(l);
+  // in dispatch order, so that the largest start first on every XCD
+  first.push_back(map.size());
+  map.resize(map.size() + p.singles.size());
+  const int ns = (int)p.singles.size();
+  for (int b = 0; b < ns; ++b) map[first.back() + (size_t)xcd_index(b, ns)] = int2{p.singles[(size_t)b], 0};
   const ResSys<ND>* dsys = reinterpret_cast<const ResSys<ND>*>(base + t.sys);
   int2* dmap = reinterpret_cast<int2*>(base + t.map);
   hipError_t e = hipMemcpyAsync(base + t.sys, h.data(), sizeof(ResSys<ND>) * h.size(), hipMemcpyHostToDevice, s);
@@ -264,15 +278,17 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go away
   if (e != hipSuccess) return e;
   kb_res_init<ND><<<dim3((unsigned)nsys, (kResWords + 255) / 256), 256, 0, s>>>(dsys);  // y is limited to 65,535
-  for (size_t l = 0; l < p.launches.size(); ++l) {
+  for (size_t l = 0; l <= p.launches.size(); ++l) {
+    const bool coop = l < p.launches.size();
     int W = 0, H = 0;
-    for (int k : p.launches[l]) {
+    for (int k : coop ? p.launches[l] : p.singles) {
       W += p.G[(size_t)k];
       H = std::max(H, p.H[(size_t)k]);
     }
+    if (W == 0) continue;
     const size_t lds = res_lds(kResBatchK, H);
-    e = opts.variant == PBCGS_BICGSTAB ? res_launch_batch_bicg(ND, dsys, dmap + first[l], W, lds, s)
-                                       : res_launch_batch_pipe(ND, dsys, dmap + first[l], W, lds, s);
+    e = opts.variant == PBCGS_BICGSTAB ? res_launch_batch_bicg(ND, dsys, dmap + first[l], W, lds, coop, s)
+                                       : res_launch_batch_pipe(ND, dsys, dmap + first[l], W, lds, coop, s);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();
@@ -280,12 +296,24 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
 
 }  // namespace
 
+constexpr int64_t kResBatchMinRows = 1024;  // mean rows of a batch of many one-workgroup systems
+
 // Largest systems first, each into the first launch with room: they iterate
-// longest, and the small ones fill the workgroups beside them.
-ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus) {
+// longest, and the small ones fill the workgroups beside them.  Systems of one
+// workgroup exchange nothing, so those that find no room share one ordinary
+// launch, whose workgroups start as others end; in cooperative launches of 256
+// they waited for each launch's slowest system (400 of 64^2, 40 iterations:
+// 4.7 ms, now 3.6, streamed 6.0).
+//
+// A batch with more of them than compute units and few rows a system streams:
+// a workgroup's 4,096 rows are mostly empty then (ms, streamed / resident:
+// 2,000 of 16^2 13.8 / 16.8, 500 of 16^2 solved to 1e-8 3.9 / 4.1, 1,000 of
+// 32^2 8.4 / 8.3).  any_size: it does not.
+ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus, bool any_size) {
   ResBatchPlan p;
   const int maxg = std::min(cus, kResMaxG);
   std::vector<int> order;
+  int64_t rows = 0;
   p.nd = 5;
   for (size_t k = 0; k < sys.size(); ++k) {
     const ResOp& op = sys[k].op;
@@ -299,6 +327,7 @@ ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus) {
     p.G.push_back((int)G);
     p.H.push_back((int)H);
     order.push_back((int)k);
+    rows += op.n;
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sys[(size_t)a].op.n > sys[(size_t)b].op.n; });
   std::vector<int> used;
@@ -306,12 +335,17 @@ ResBatchPlan res_batch_plan(const std::vector<ResBatchSys>& sys, int cus) {
     size_t l = 0;
     while (l < used.size() && used[l] + p.G[(size_t)k] > maxg) ++l;
     if (l == used.size()) {
+      if (p.G[(size_t)k] == 1) {
+        p.singles.push_back(k);
+        continue;
+      }
       used.push_back(0);
       p.launches.emplace_back();
     }
     used[l] += p.G[(size_t)k];
     p.launches[l].push_back(k);
   }
+  if (!any_size && (int)p.singles.size() > maxg && rows < kResBatchMinRows * (int64_t)sys.size()) return p;
   p.ok = true;
   return p;
 }
@@ -367,6 +401,16 @@ hipError_t res_batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys
   *err_word = reinterpret_cast<int32_t*>(base + t.err);
   if (p.nd <= 5) return batch_launch<5>(p, sys, opts, base, t, s);
   return batch_launch<7>(p, sys, opts, base, t, s);
+}
+
+hipError_t res_batch_copy_x(const ResBatchPlan& p, const std::vector<ResBatchSys>& sys, void* tables, hipStream_t s) {
+  char* d = static_cast<char*>(tables) + batch_tables(p).sys;
+  int32_t nmax = 0;
+  for (const ResBatchSys& y : sys) nmax = std::max(nmax, y.op.n);
+  const dim3 g((unsigned)sys.size(), (unsigned)std::min((nmax + 1023) / 1024, 64));
+  if (p.nd <= 5) kb_res_copy_x<5><<<g, 256, 0, s>>>(reinterpret_cast<const ResSys<5>*>(d));
+  else kb_res_copy_x<7><<<g, 256, 0, s>>>(reinterpret_cast<const ResSys<7>*>(d));
+  return hipGetLastError();
 }
 
 bool res_method(int32_t variant) { return variant != PBCGS_CA_BICGSTAB; }

@@ -105,10 +105,11 @@ __device__ __forceinline__ void uniform(State& s) {
 }
 
 // XCD-contiguous index of a launch's workgroup: workgroup b runs on XCD b % 8.
-__device__ __forceinline__ int xcd_index() {
-  const int b = (int)blockIdx.x, G = (int)gridDim.x, q = G >> 3, r = G & 7, x = b & 7;
-  return x * q + min(x, r) + (b >> 3);
+__host__ __device__ __forceinline__ int xcd_index(int b, int G) {
+  const int q = G >> 3, r = G & 7, x = b & 7;
+  return x * q + (x < r ? x : r) + (b >> 3);
 }
+__device__ __forceinline__ int xcd_index() { return xcd_index((int)blockIdx.x, (int)gridDim.x); }
 
 // One system of a batched launch.
 template <int ND>
@@ -635,12 +636,14 @@ inline hipError_t res_go(void (*k)(ResOpT<ND>, ResArgs), int K, const ResPlan& p
 
 template <int ND>
 inline hipError_t res_go_batch(void (*k)(const ResSys<ND>*, const int2*), const void* sys, const int2* map, int workgroups,
-                               size_t lds, hipStream_t s) {
+                               size_t lds, bool coop, hipStream_t s) {
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)lds);
   if (e != hipSuccess) return e;
   const ResSys<ND>* p = static_cast<const ResSys<ND>*>(sys);
   void* args[] = {&p, &map};
+  if (!coop)
+    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3((unsigned)workgroups), dim3(kResT), args, lds, s);
   return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k), dim3((unsigned)workgroups), dim3(kResT), args,
                                     (unsigned)lds, s);
 }

@@ -165,9 +165,10 @@ hipError_t res_launch_bicg(const ResPlan& p, const ResOp& op, const ResJob& j, h
   });
 }
 
-hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, hipStream_t s) {
-  if (nd <= 5) return res_go_batch<5>(&kb_res_bicg<5>, sys, map, workgroups, lds, s);
-  return res_go_batch<7>(&kb_res_bicg<7>, sys, map, workgroups, lds, s);
+hipError_t res_launch_batch_bicg(int nd, const void* sys, const int2* map, int workgroups, size_t lds, bool coop,
+                                 hipStream_t s) {
+  if (nd <= 5) return res_go_batch<5>(&kb_res_bicg<5>, sys, map, workgroups, lds, coop, s);
+  return res_go_batch<7>(&kb_res_bicg<7>, sys, map, workgroups, lds, coop, s);
 }
 
 }  // namespace pbcgs

@@ -48,7 +48,9 @@ def test_more_systems_than_a_grid_has_rows(variant, monkeypatch):
 
 
 def test_memory_of_many_small_systems(monkeypatch):
-    """3,000 systems of 100 rows take no more device memory in the resident form than streamed."""
+    """3,000 systems of 100 rows take no more device memory in the resident
+    form than streamed, beyond what 300 of them take (a queue's first launch
+    of a kernel allocates that kernel's scratch, whatever the batch)."""
     require_gpu()
     used = []
     for mode in ("0", "1"):
@@ -57,9 +59,31 @@ def test_memory_of_many_small_systems(monkeypatch):
         A = tridiagonal(100, ctx)
         b = torch.ones(3000, 100, dtype=torch.float64, device="cuda")
         x = torch.empty_like(b)
+        bs, outs = list(b.unbind(0)), list(x.unbind(0))
+        solver.solve_batched([A] * 300, bs[:300], outs=outs[:300], maxit=3)
         torch.cuda.synchronize()
         before = torch.cuda.mem_get_info()[0]
-        solver.solve_batched([A] * 3000, list(b.unbind(0)), outs=list(x.unbind(0)), maxit=3)
+        solver.solve_batched([A] * 3000, bs, outs=outs, maxit=3)
         used.append(before - torch.cuda.mem_get_info()[0])
     say(f"bytes taken: streamed {used[0]}, resident {used[1]}")
     assert used[1] <= used[0] + (4 << 20)
+
+
+def test_which_batches_stream():
+    """Many small systems stream, where a workgroup of the resident form would
+    be mostly empty; batches that one launch holds, and larger systems, do not.
+    The leftover systems' bits are the streamed ones."""
+    require_gpu()
+    ctx = solver.Context()
+    for n, count, resident in ((100, 300, False), (100, 200, True), (2000, 300, True)):
+        A = tridiagonal(n, ctx)
+        g = torch.Generator(device="cuda").manual_seed(n)
+        b = torch.randn(count, n, dtype=torch.float64, device="cuda", generator=g)
+        out = []
+        for graph in (True, False):  # the second: streamed
+            x = torch.empty_like(b)
+            _, infos = solver.solve_batched([A] * count, list(b.unbind(0)), outs=list(x.unbind(0)), maxit=12,
+                                            rr_period=5, graph=graph)
+            assert {i.resident_rows > 0 for i in infos} == {resident and graph}, (n, count, graph)
+            out.append((x.cpu().numpy(), [(i.iters, i.n_rr, i.status, i.relres_rec, i.relres_true) for i in infos]))
+        assert same(out[0][0], out[1][0]) and out[0][1] == out[1][1], (n, count)
