@@ -571,6 +571,7 @@ int true_relres(pbcgs_ctx_t ctx, const Op& op, const Args& a0, double rho0, doub
 // ---------------------------------------------------------------------------
 // Per-(operator, preconditioner) driver.
 // ---------------------------------------------------------------------------
+constexpr int32_t kViMinRows = 1 << 18;  // rows from which layouts are read as value codes (see vi_operator)
 constexpr int32_t kManyRows = 1 << 21;  // see Driver::take_many
 constexpr int kManyR = 4;
 constexpr int kFirstChunk = 8;  // iterations of a CSR-stream solve's first two chunks
@@ -1220,7 +1221,20 @@ bool resident_options(pbcgs_ctx_t ctx, const pbcgs_opts& o) {
   }
   return ctx->coop == 1;
 }
+// A budget of few iterations does not pay for what a resident solve costs
+// beside its launch (the uniformity kernels, the cleared words, x's copy).
+// Single solves of fewer than 2^18 rows, above which the streamed kernels set
+// up more than that (ms, streamed / resident, 0, 1 and 3 iterations of
+// p-BiCGStab: 41^3 0.110 / 0.146, 0.148 / 0.152, 0.178 / 0.170; 64^3 0.220 /
+// 0.155, 0.266 / 0.166), and batches (16 of 64^2, 1 and 3 iterations: 0.262 /
+// 0.314, 0.302 / 0.328; 300 of 64^2, 3: 2.20 / 2.33).
+constexpr int32_t kResMinMaxit = 2, kResBatchMinMaxit = 8;
+bool resident_budget(const pbcgs_opts& o, int32_t min_maxit) {
+  return o.maxit >= min_maxit || env_int("PBCGS_PERSIST", -1) == 1;
+}
+
 bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o) {
+  if (A->n < kViMinRows && !resident_budget(o, kResMinMaxit)) return false;
   const bool layout = A->kind == OP_CSR && A->ndia > 0 && A->ndia <= kResMaxND;
   return (layout || A->kind == OP_ST5 || A->kind == OP_ST7) && resident_options(ctx, o);
 }
@@ -2092,7 +2106,6 @@ static DiaOpC cached_loads(const DiaOp& d) {
 // per row cost more than their bytes saved (2-D 64^2: 13.1 against 12.4 us
 // per iteration; 16^3 to 48^3 within 0.3-1.5 us; 96^3: 43.9 against 52.9).
 // One host synchronisation reads the overflow word.
-constexpr int32_t kViMinRows = 1 << 18;
 template <class V>
 static bool vi_operator(pbcgs_ctx_t ctx, const DiaOpT<V>& d, DiaViOpT<V>* out, int slot = 0) {
   const int mode = env_int("PBCGS_VALUE_CODES", -1);
@@ -2942,7 +2955,7 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
   // launches over the whole batch.  Whatever it cannot have (memory for its
   // tables, a launch) leaves the batch to the streamed kernels.
   bool resident = false;
-  if (dia && resident_options(ctx, o)) {
+  if (dia && resident_budget(o, kResBatchMinMaxit) && resident_options(ctx, o)) {
     std::vector<ResBatchSys> rsys;
     for (int32_t k = 0; k < nsys; ++k) {
       ResBatchSys y;

@@ -68,10 +68,25 @@ def test_batches(variant, monkeypatch):
     require_gpu()
     ops = [solver.csr(*solver.assemble_convdiff(2, n, 5, (20.0, 10.0))) for n in (512, 256, 64)]
     bs = [dev_t(np.ones(A.n)) for A in ops]
-    kw = dict(variant=variant, maxit=4)
+    kw = dict(variant=variant, maxit=8)
     assert [i.resident_rows for i in solver.solve_batched(ops, bs, **kw)[1]] == [8, 8, 8]
     ops.append(csr_op(band(2000, [-40, -1, 1, 40], True)))
     bs.append(dev_t(np.ones(2000)))
     assert [i.resident_rows for i in solver.solve_batched(ops, bs, **kw)[1]] == [0, 0, 0, 0]
     monkeypatch.setenv("PBCGS_PERSIST", "0")
     assert [i.resident_rows for i in solver.solve_batched(ops[:3], bs[:3], **kw)[1]] == [0, 0, 0]
+
+
+def test_short_budgets_stream(monkeypatch):
+    """A budget too short to pay for what lies beside a resident launch streams, where that is cheaper."""
+    require_gpu()
+    small = csr_op(band(3000, [-40, -1, 1, 40], False))
+    large = solver.stencil(512, 512, 1, (-1.0, -1.25, 4.5, -0.999, -0.75))
+    for variant in ALG:
+        assert [ran(small, variant=variant, maxit=m) > 0 for m in (0, 1, 2)] == [False, False, True], variant
+        assert ran(large, variant=variant, maxit=0) > 0, variant
+    ops, bs = [small] * 3, [dev_t(np.ones(3000))] * 3
+    for m in (0, 7, 8):
+        assert {i.resident_rows > 0 for i in solver.solve_batched(ops, bs, maxit=m)[1]} == {m == 8}, m
+    monkeypatch.setenv("PBCGS_PERSIST", "1")
+    assert ran(small, maxit=0) > 0 and solver.solve_batched(ops, bs, maxit=0)[1][0].resident_rows > 0
