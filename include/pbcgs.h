@@ -349,8 +349,9 @@ int pbcgs_jacobi_dinv(pbcgs_ctx_t ctx, pbcgs_op_t A, double* dinv);
  * diagonals whose values vary up to 2^18 rows.  Same results, bit for bit.
  * opts.flags bits 0, 1, 3 and 4, the perturbation hook and the allocation-free
  * entry point keep the streamed kernels, and so does a launch that the device
- * refuses or that finds the device busy for about a second (the solve then
- * starts again from x_0, which the resident launch does not touch).
+ * refuses or that finds the device busy for about 0.07 s (the solve then
+ * starts again from x_0, which the resident launch does not touch; the
+ * context's next 16 such solves stream, 32 after a second one in a row).
  * Streamed solves of more than 2^21 rows (binary64 p-BiCGStab: 2^22) launch
  * workgroups of 1,024 rows whatever shape was tuned.
  */

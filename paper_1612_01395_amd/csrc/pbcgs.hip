@@ -100,6 +100,8 @@ struct pbcgs_ctx_s {
   unsigned char* bres = nullptr;  // batched resident solves: tables
   size_t bres_cap = 0;            // bytes
   bool streamed_only = false;     // the autotuners time the streamed kernels
+  int32_t res_skip = 0;           // solves to stream after a resident one gave up (see resident_gave_up)
+  int32_t res_backoff = 0;
   unsigned char* res = nullptr;  // resident solves: exchange words, then kResAux bytes
   int32_t* hflag = nullptr; // pinned host copy
   double* part = nullptr;   // PB_COUNT buffers of kMaxD * kMaxG partial sums
@@ -1219,8 +1221,23 @@ bool resident_options(pbcgs_ctx_t ctx, const pbcgs_opts& o) {
     int v = 0;
     ctx->coop = (hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, ctx->device) == hipSuccess && v) ? 1 : 0;
   }
-  return ctx->coop == 1;
+  if (ctx->coop != 1) return false;
+  if (mode < 0 && ctx->res_skip > 0) {
+    --ctx->res_skip;
+    return false;
+  }
+  return true;
 }
+
+// A resident solve whose waits timed out (another process holds part of the
+// device, say) has cost about 0.07 s: the context's next 16 solves that
+// could be resident stream, and twice as many after each further one that
+// gives up, until one runs to its end.
+void resident_gave_up(pbcgs_ctx_t ctx) {
+  ctx->res_backoff = std::min(std::max(2 * ctx->res_backoff, 16), 4096);
+  ctx->res_skip = ctx->res_backoff;
+}
+
 // A budget of few iterations does not pay for what a resident solve costs
 // beside its launch (the uniformity kernels, the cleared words, x's copy).
 // Single solves of fewer than 2^18 rows, above which the streamed kernels set
@@ -1294,13 +1311,15 @@ ResJob resident_job(const pbcgs_opts& o) {
   j.maxit = o.maxit;
   j.aform = alpha_form(o);
   j.tol = o.tol;
+  j.give_up = env_int("PBCGS_RESIDENT_GIVE_UP", 0);
   return j;
 }
 
 // Runs the solve from x_0 (its folded form y_0 when `fold` is set, see
 // k_fold_x) and leaves the iterate in ctx->ws; *done = false, with nothing of
-// the caller's written, when it did not run to its end (a launch refused, or a
-// wait that timed out because the device was busy for about a second).
+// the caller's written but entries of the history (which the streamed solve
+// writes again), when it did not run to its end (a launch refused, or a wait
+// that timed out because the device was busy for about 0.07 s).
 int run_resident(pbcgs_ctx_t ctx, const ResPlan& plan, const ResOp& op, const Args& a, const pbcgs_opts& o, int pc,
                  const double* fold_dv, double fold_ds, bool fold, pbcgs_info* info, double* rho0, bool* done) {
   hipStream_t s = ctx->stream;
@@ -1333,7 +1352,11 @@ int run_resident(pbcgs_ctx_t ctx, const ResPlan& plan, const ResOp& op, const Ar
   DevState fin;
   const int rc = read_state(ctx, 0, &fin);
   if (rc != PBCGS_SUCCESS) return rc;
-  if (fin.pad[0] != 0 || fin.status < 0) return PBCGS_SUCCESS;
+  if (fin.pad[0] != 0 || fin.status < 0) {
+    resident_gave_up(ctx);
+    return PBCGS_SUCCESS;
+  }
+  ctx->res_backoff = 0;
   HIP_TRY(ctx, hipMemcpyAsync(a.x, res_x(j), sizeof(double) * (size_t)a.n, hipMemcpyDeviceToDevice, s));
   float ms = 0.f;
   (void)hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop);
@@ -1515,7 +1538,11 @@ int run_resident_batch(pbcgs_ctx_t ctx, const pbcgs_opts& o, const ResBatchPlan&
   }
   HIP_TRY(ctx, hipMemcpyAsync(ctx->hflag, err, sizeof *err, hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
-  if (*ctx->hflag != 0) return PBCGS_SUCCESS;
+  if (*ctx->hflag != 0) {
+    resident_gave_up(ctx);
+    return PBCGS_SUCCESS;
+  }
+  ctx->res_backoff = 0;
   HIP_TRY(ctx, res_batch_copy_x(plan, sys, ctx->bres, s));
   *done = true;
   return PBCGS_SUCCESS;

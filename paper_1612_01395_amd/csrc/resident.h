@@ -35,6 +35,8 @@ struct ResOp {
 
 struct ResJob {
   int32_t variant, rr_period, rr_max, maxit, aform;
+  int32_t give_up;       // test hook: 1: the workgroups wait for one that is not there and time out (about
+                         // 0.07 s; needs 2 to 255 workgroups); 2: the solve counts as timed out at its end
   double tol;
   bool pc;               // Jacobi applied as the algorithms write it
   const double* dinv;    // its vector, or nullptr: the constant dinv_s
@@ -45,7 +47,7 @@ struct ResJob {
   double* vecs;          // kResVecs vectors of `stride` doubles, 16-byte aligned
   int64_t stride;        // >= n + kResVecPad, even
   unsigned long long* words;  // kResWords
-  int32_t* err;          // set to 1 when a wait timed out (nothing was written then)
+  int32_t* err;          // set to 1 when a wait timed out (of the caller's, only hist is written then)
   DevState* st;          // the final state
 };
 

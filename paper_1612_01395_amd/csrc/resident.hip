@@ -90,11 +90,11 @@ ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus) {
 
 // Clears the exchange words, the error word and the state's status (which a
 // finished solve overwrites).
-__global__ __launch_bounds__(256) void k_res_init(u64* words, int32_t* err, DevState* st) {
+__global__ __launch_bounds__(256) void k_res_init(u64* words, int32_t* err, DevState* st, int32_t give_up) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < kResWords) words[i] = 0;
   if (i == 0) {
-    *err = 0;
+    *err = give_up == 2 ? 1 : 0;
     st->status = -1;
   }
 }
@@ -211,12 +211,12 @@ __global__ __launch_bounds__(256) void kb_uniform_check(const UniformArgs* us) {
 }
 
 template <int ND>
-__global__ __launch_bounds__(256) void kb_res_init(const ResSys<ND>* sys) {
+__global__ __launch_bounds__(256) void kb_res_init(const ResSys<ND>* sys, int32_t give_up) {
   const ResArgs& a = sys[blockIdx.x].a;
   const int i = blockIdx.y * 256 + threadIdx.x;
   if (a.G > 1 && i < kResWords) a.words[i] = 0;
   if (i == 0) {
-    *a.err = 0;
+    *a.err = give_up == 2 ? 1 : 0;
     a.st->status = -1;
   }
 }
@@ -277,7 +277,8 @@ hipError_t batch_launch(const ResBatchPlan& p, const std::vector<ResBatchSys>& s
   if (e == hipSuccess) e = hipMemcpyAsync(dmap, map.data(), sizeof(int2) * map.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go away
   if (e != hipSuccess) return e;
-  kb_res_init<ND><<<dim3((unsigned)nsys, (kResWords + 255) / 256), 256, 0, s>>>(dsys);  // y is limited to 65,535
+  // the systems in x: y is limited to 65,536
+  kb_res_init<ND><<<dim3((unsigned)nsys, (kResWords + 255) / 256), 256, 0, s>>>(dsys, opts.give_up);
   for (size_t l = 0; l <= p.launches.size(); ++l) {
     const bool coop = l < p.launches.size();
     int W = 0, H = 0;
@@ -416,7 +417,7 @@ hipError_t res_batch_copy_x(const ResBatchPlan& p, const std::vector<ResBatchSys
 bool res_method(int32_t variant) { return variant != PBCGS_CA_BICGSTAB; }
 
 hipError_t res_launch(const ResPlan& p, const ResOp& op, const ResJob& j, hipStream_t s) {
-  k_res_init<<<(kResWords + 255) / 256, 256, 0, s>>>(j.words, j.err, j.st);
+  k_res_init<<<(kResWords + 255) / 256, 256, 0, s>>>(j.words, j.err, j.st, j.give_up);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   switch (j.variant) {

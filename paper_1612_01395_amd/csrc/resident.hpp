@@ -33,7 +33,7 @@
 //
 // Every wait is bounded: a workgroup that polls kResSpin times without success
 // sets job.err and leaves, and so do the others in turn; the caller's x is not
-// touched by this kernel.
+// touched by this kernel (its history is: the entries of the iterations done).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -51,7 +51,7 @@ typedef double D2 __attribute__((ext_vector_type(2)));
 typedef double D2u __attribute__((ext_vector_type(2), aligned(8)));
 typedef unsigned U4 __attribute__((ext_vector_type(4)));
 
-constexpr int kResSpin = 1 << 19;  // polls before a wait gives up (about a second)
+constexpr int kResSpin = 1 << 19;  // polls before a wait gives up (0.07 s, measured)
 constexpr int kResFront = 2;       // doubles before row 0 in an exchange buffer
 constexpr int kSc1 = 16;           // buffer cache policy: agent scope
 
@@ -594,7 +594,7 @@ inline ResOpT<ND> res_op(const ResOp& o) {
 
 inline ResArgs res_args(const ResPlan& p, const ResJob& j) {
   ResArgs a = {};
-  a.G = p.G;
+  a.G = p.G + (j.give_up == 1 && p.G > 1 && p.G < kResMaxG ? 1 : 0);
   a.H = p.H;
   a.reach = p.reach;
   a.variant = j.variant;

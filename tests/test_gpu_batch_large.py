@@ -27,7 +27,7 @@ def tridiagonal(n, ctx):
 
 @pytest.mark.parametrize("variant", ["pbicgstab_rr", "bicgstab"])
 def test_more_systems_than_a_grid_has_rows(variant, monkeypatch):
-    """66,000 systems: more than the 65,535 a launch takes in its second grid dimension."""
+    """66,000 systems: more than the 65,536 a launch takes in its second grid dimension."""
     require_gpu()
     count, n = 66000, 5
     ctx = solver.Context()
