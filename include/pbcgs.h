@@ -347,8 +347,11 @@ int pbcgs_jacobi_dinv(pbcgs_ctx_t ctx, pbcgs_op_t A, double* dinv);
  * launch that keeps the Krylov vectors in registers and LDS; p-BiCGStab and
  * BiCGStab with Jacobi as written and p-CG with Jacobi up to 2^20 rows, and
  * diagonals whose values vary up to 2^18 rows.  Same results, bit for bit.
- * opts.flags bits 0, 1, 3 and 4, the perturbation hook and the allocation-free
- * entry point keep the streamed kernels, and so does a launch that the device
+ * opts.check_every does not apply to it: nothing is polled while it runs.
+ * opts.flags bits 0, 1, 3 and 4, a maxit above 200,000 (a launch cannot be
+ * interrupted), budgets too short to pay for it (maxit < 2 below 2^18 rows,
+ * < 8 in batches), the perturbation hook and the allocation-free entry point
+ * keep the streamed kernels, and so does a launch that the device
  * refuses or that finds the device busy for about 0.07 s (the solve then
  * starts again from x_0, which the resident launch does not touch; the
  * context's next 16 such solves stream, 32 after a second one in a row).

@@ -1205,11 +1205,16 @@ struct Driver {
 // environment), the perturbation hook and the allocation-free entry point keep
 // those.  PBCGS_PERSIST=0 never takes the resident form, =1 also with the
 // environment's switches set.
+//
+// One launch cannot be interrupted and may hold every compute unit, so its
+// budget is bounded: 200,000 iterations of up to 42 us are 8 s (1e8 would be
+// over an hour); larger budgets stream, in launches other work can run between.
+constexpr int32_t kResMaxMaxit = 200000;
 bool resident_options(pbcgs_ctx_t ctx, const pbcgs_opts& o) {
   if (ctx->noalloc || ctx->streamed_only || ctx->perturb_iter >= 0 || o.precision != PBCGS_FP64 ||
       (o.flags & (1 | 2 | 8 | 16)))
     return false;
-  if (!res_method(o.variant) || o.maxit > 100000000) return false;  // exchange numbers stay in 32 bits
+  if (!res_method(o.variant) || o.maxit > kResMaxMaxit) return false;
   const int mode = env_int("PBCGS_PERSIST", -1);
   if (mode == 0) return false;
   if (mode < 0) {

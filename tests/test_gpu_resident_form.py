@@ -90,3 +90,14 @@ def test_short_budgets_stream(monkeypatch):
         assert {i.resident_rows > 0 for i in solver.solve_batched(ops, bs, maxit=m)[1]} == {m == 8}, m
     monkeypatch.setenv("PBCGS_PERSIST", "1")
     assert ran(small, maxit=0) > 0 and solver.solve_batched(ops, bs, maxit=0)[1][0].resident_rows > 0
+
+
+def test_budgets_one_launch_may_hold():
+    """Budgets above 200,000 iterations stream: a launch cannot be interrupted."""
+    require_gpu()
+    op = csr_op(band(3000, [-40, -1, 1, 40], False))
+    for variant in ALG:
+        assert [ran(op, variant=variant, maxit=m) > 0 for m in (200000, 200001)] == [True, False], variant
+    ops, bs = [op] * 3, [dev_t(np.ones(3000))] * 3
+    for m in (200000, 200001):
+        assert {i.resident_rows > 0 for i in solver.solve_batched(ops, bs, maxit=m)[1]} == {m == 200000}, m
