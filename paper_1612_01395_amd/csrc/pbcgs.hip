@@ -1261,7 +1261,8 @@ bool resident_allowed(pbcgs_ctx_t ctx, const pbcgs_op_s* A, const pbcgs_opts& o)
   return (layout || A->kind == OP_ST5 || A->kind == OP_ST7) && resident_options(ctx, o);
 }
 
-// The operator's structure in the resident form (values left out).
+// The operator's structure in the resident form (values left out); a layout of
+// more than kResMaxND diagonals does not fit a ResOp and must not come here.
 ResOp resident_structure(const pbcgs_op_s* A) {
   ResOp r;
   std::memset(&r, 0, sizeof r);
@@ -2987,7 +2988,9 @@ int pbcgs_solve_batched(pbcgs_ctx_t ctx, int32_t nsys, const pbcgs_op_t* A, cons
   // launches over the whole batch.  Whatever it cannot have (memory for its
   // tables, a launch) leaves the batch to the streamed kernels.
   bool resident = false;
-  if (dia && resident_budget(o, kResBatchMinMaxit) && resident_options(ctx, o)) {
+  bool few = dia;  // every system's diagonals fit the resident form's tables
+  for (int32_t k = 0; k < nsys && few; ++k) few = A[k]->ndia <= kResMaxND;
+  if (few && resident_budget(o, kResBatchMinMaxit) && resident_options(ctx, o)) {
     std::vector<ResBatchSys> rsys;
     for (int32_t k = 0; k < nsys; ++k) {
       ResBatchSys y;

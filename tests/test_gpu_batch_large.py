@@ -6,10 +6,14 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+
 from paper_1612_01395_amd import solver
-from gpu_util import require_gpu, same, say
+from gpu_util import csr_op, dev_t, host, require_gpu, same, say
 
 pytestmark = pytest.mark.gpu
+
+ALG = {"bicgstab": oracle.ALG_BICGSTAB, "pbicgstab_rr": oracle.ALG_PBICGSTAB_RR}
 
 
 def tridiagonal(n, ctx):
@@ -87,3 +91,36 @@ def test_which_batches_stream():
             assert {i.resident_rows > 0 for i in infos} == {resident and graph}, (n, count, graph)
             out.append((x.cpu().numpy(), [(i.iters, i.n_rr, i.status, i.relres_rec, i.relres_true) for i in infos]))
         assert same(out[0][0], out[1][0]) and out[0][1] == out[1][1], (n, count)
+
+
+@pytest.mark.parametrize("variant", list(ALG))
+@pytest.mark.parametrize("diagonals", [7, 8, 27, 32])
+def test_layouts_of_many_diagonals(diagonals, variant):
+    """Layouts of more than seven diagonals have no place in the resident
+    form's tables: such a batch streams, whatever stands beside them."""
+    require_gpu()
+    rng = np.random.default_rng(diagonals)
+    n = 2000
+    offs = np.sort(np.concatenate([[0], 1 + rng.choice(120, diagonals - 1, replace=False)]))
+    rows, cols, vals = [], [], []
+    for o in offs:
+        r = np.arange(n - o)
+        rows.append(r)
+        cols.append(r + o)
+        vals.append(np.full(r.size, 40.0 if o == 0 else -0.5))
+    r, c, v = (np.concatenate(a) for a in (rows, cols, vals))
+    order = np.lexsort((c, r))
+    wide = oracle.CSR(np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int32),
+                      c[order].astype(np.int32), v[order])
+    grid = oracle.assemble(2, 20, 5, (20.0, 10.0))
+    As = [grid, wide, grid]
+    ops = [csr_op(A) for A in As]
+    assert ops[1].diagonals == diagonals
+    bs = [rng.standard_normal(A.n) for A in As]
+    kw = dict(tol=1e-9, maxit=30, rr_period=7)
+    xs, infos = solver.solve_batched(ops, [dev_t(b) for b in bs], variant=variant, **kw)
+    for A, b, x, info in zip(As, bs, xs, infos):
+        x_or, i_or = oracle.solve(A, b, algo=ALG[variant], **kw)
+        assert (info.resident_rows > 0) == (diagonals <= 7)
+        assert (info.status, info.iters, info.n_rr) == (i_or["status"], i_or["iters"], i_or["n_rr"])
+        assert same(host(x), x_or)
