@@ -92,7 +92,8 @@ struct pbcgs_ctx_s {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   DevState* st = nullptr;   // state slots (device): 0, 1 solver ring; 2, 3 utility reductions
-  DevState* hst = nullptr;  // pinned host copies: slots 0, 1 for polling, 2 for reads of a state or a scalar
+  DevState* hst = nullptr;  // pinned host copies: slots 0, 1 for polling, 2 for reads of a state or a scalar,
+                            // 3 for resident_uniform
   int32_t* flag = nullptr;  // structural error flags of utility kernels
   int coop = -1;            // device supports cooperative launches (-1: not asked yet)
   double* bigpart = nullptr;     // partial sums of launches of more than kMaxG workgroups
@@ -1290,22 +1291,26 @@ ResOp resident_structure(const pbcgs_op_s* A) {
   return r;
 }
 
-// One value per diagonal of the CSR operator (of A M^{-1} when folded)?  Then
-// they go into op->c.  One host synchronisation.
-int resident_uniform(pbcgs_ctx_t ctx, const pbcgs_op_s* A, int pc_fold, const double* dv, double ds, ResOp* op,
-                     bool* uniform) {
+// One value per diagonal of the CSR operator (of A M^{-1} when folded)?  Queues
+// the question; resident_uniform() reads the answer once the stream has been
+// synchronised.
+int resident_ask(pbcgs_ctx_t ctx, const pbcgs_op_s* A, int pc_fold, const double* dv, double ds, const ResOp& op) {
   unsigned char* aux = ctx->res + kResWords * sizeof(unsigned long long);
-  HIP_TRY(ctx, res_uniform(*op, A->rp, A->ci, A->va, pc_fold == PC_VEC ? dv : nullptr, pc_fold == PC_NONE, ds, aux,
+  HIP_TRY(ctx, res_uniform(op, A->rp, A->ci, A->va, pc_fold == PC_VEC ? dv : nullptr, pc_fold == PC_NONE, ds, aux,
                            ctx->stream));
   static_assert(sizeof(DevState) >= kResAux, "the pinned slot holds the result");
-  HIP_TRY(ctx, hipMemcpyAsync(&ctx->hst[2], aux, kResAux, hipMemcpyDeviceToHost, ctx->stream));
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  const unsigned char* h = reinterpret_cast<const unsigned char*>(&ctx->hst[2]);
+  HIP_TRY(ctx, hipMemcpyAsync(&ctx->hst[3], aux, kResAux, hipMemcpyDeviceToHost, ctx->stream));
+  return PBCGS_SUCCESS;
+}
+
+// The answer: 0, and the values in op->c, or kResVaries with kResManyValues.
+int32_t resident_uniform(pbcgs_ctx_t ctx, ResOp* op) {
+  static_assert(kResCodes == kViTab, "the codes' table");
+  const unsigned char* h = reinterpret_cast<const unsigned char*>(&ctx->hst[3]);
   int32_t flag;
   std::memcpy(&flag, h + 8 * kResMaxND, sizeof flag);
-  *uniform = flag == 0;
-  if (*uniform) std::memcpy(op->c, h, sizeof(double) * op->nd);
-  return PBCGS_SUCCESS;
+  if (flag == 0) std::memcpy(op->c, h, sizeof(double) * op->nd);
+  return flag;
 }
 
 ResJob resident_job(const pbcgs_opts& o) {
@@ -1842,7 +1847,7 @@ int pbcgs_ctx_create(int device, void* hip_stream, pbcgs_ctx_t* out) {
             hipMalloc(&c->part, sizeof(double) * kMaxD * kMaxG * PB_COUNT) == hipSuccess &&
             hipMalloc(&c->flag, 64) == hipSuccess &&
             hipMalloc(&c->res, kResWords * sizeof(unsigned long long) + kResAux) == hipSuccess &&
-            hipHostMalloc(&c->hst, 3 * sizeof(DevState), hipHostMallocDefault) == hipSuccess &&
+            hipHostMalloc(&c->hst, 4 * sizeof(DevState), hipHostMallocDefault) == hipSuccess &&
             hipHostMalloc(&c->hflag, 64, hipHostMallocDefault) == hipSuccess &&
             hipEventCreate(&c->ev_start) == hipSuccess && hipEventCreate(&c->ev_stop) == hipSuccess &&
             hipEventCreateWithFlags(&c->ev_poll[0], hipEventDisableTiming) == hipSuccess &&
@@ -2480,6 +2485,23 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
   double* v[nvec];
   for (int k = 0; k < nvec; ++k) v[k] = ctx->ws + (size_t)k * np;
 
+  // Resident form (see resident_options): whether a CSR operator's diagonals
+  // hold one value each is asked before the preconditioner's own question, so
+  // that one synchronisation answers both; a folded operator's values are known
+  // only after it.
+  ResOp rop;
+  ResPlan plan;
+  bool asked = false;
+  if (resident_allowed(ctx, A, o)) {
+    rop = resident_structure(A);
+    plan = res_plan(rop, o.variant, o.precond == PBCGS_PRECOND_JACOBI, ctx->cus);
+    if (plan.K > 0 && A->kind == OP_CSR && o.precond == PBCGS_PRECOND_JACOBI) {
+      rc = resident_ask(ctx, A, PC_NONE, nullptr, 0.0, rop);
+      if (rc != PBCGS_SUCCESS) return rc;
+      asked = true;
+    }
+  }
+
   // preconditioner mode: none, a vector of 1/a_ii, or one constant
   int pc = PC_NONE;
   const double* dinv_vec = nullptr;  // the vector of 1/a_ii when there is one (also when constant)
@@ -2538,20 +2560,25 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
     a.zh = hat ? v[11] : a.z;
   }
 
-  if (resident_allowed(ctx, A, o)) {
+  bool codes = true;  // value codes are not ruled out
+  if (plan.K > 0) {
     const int pcl = folded ? PC_NONE : pc;  // Jacobi applied as written
     const double ds = a.dinv_s;
     const double* fdv = (folded && pc == PC_VEC) ? dinv_vec : nullptr;
-    ResOp rop = resident_structure(A);
-    ResPlan plan = res_plan(rop, o.variant, pcl != PC_NONE, ctx->cus);
     bool uniform = true;
     if (A->kind != OP_CSR) {
       for (int d = 0; d < rop.nd; ++d) rop.c[d] = folded ? A->coef[d] * ds : A->coef[d];
-    } else if (plan.K > 0) {
-      rc = resident_uniform(ctx, A, folded ? pc : PC_NONE, fdv, ds, &rop, &uniform);
-      if (rc != PBCGS_SUCCESS) return rc;
+    } else {
+      if (!asked) {
+        rc = resident_ask(ctx, A, folded ? pc : PC_NONE, fdv, ds, rop);
+        if (rc != PBCGS_SUCCESS) return rc;
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+      }
+      const int32_t flag = resident_uniform(ctx, &rop);
+      uniform = flag == 0;
+      codes = (flag & kResManyValues) == 0;
     }
-    if (plan.K > 0 && !uniform) {
+    if (!uniform) {
       // varying values are read from the layout each time: where the solve
       // would read them as codes (2^18 rows and more) those are the better form
       if (A->n < kViMinRows) {
@@ -2694,7 +2721,7 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
           const int rcd = dia_operator<double>(ctx, A, pc, dv, ds, &dop);
           if (rcd != PBCGS_SUCCESS) return rcd;
           DiaViOp vop;
-          if (vi_operator(ctx, dop, &vop)) {
+          if (codes && vi_operator(ctx, dop, &vop)) {
             info->value_codes = 1;
             return run_folded(vop);
           }
@@ -2713,7 +2740,7 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
     // value-indexed without a preconditioner and with Jacobi by a constant
     // diagonal (a scalar); a Jacobi vector keeps the values
     DiaViOp vop;
-    if (pc != PC_VEC && vi_operator(ctx, dop, &vop)) {
+    if (codes && pc != PC_VEC && vi_operator(ctx, dop, &vop)) {
       info->value_codes = 1;
       if (pc == PC_NONE) return Driver<DiaViOp, PC_NONE>(ctx, vop, a, o).run(info);
       return Driver<DiaViOp, PC_SCALAR>(ctx, vop, a, o).run(info);

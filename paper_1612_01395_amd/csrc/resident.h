@@ -66,9 +66,14 @@ ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus);
 // Whether the resident form implements a method (PBCGS_BICGSTAB ...).
 bool res_method(int32_t variant);
 
+// What res_uniform says of an operator (0: one value per diagonal).
+// kResManyValues: some diagonal holds more than kResCodes values; not set, it
+// may nevertheless.
+constexpr int32_t kResVaries = 1, kResManyValues = 2;
+constexpr int kResCodes = 16;  // values per diagonal of the value-indexed layout
+
 // Writes to aux (kResAux device bytes) the value of each diagonal of the CSR
-// operator (rp, ci, va; op.mask its diagonals) and 0 after them when every row
-// holds that value, else 1.  plain: the stored values; else each times dinv of
+// operator (rp, ci, va; op.mask its diagonals) and after them a flag word.  plain: the stored values; else each times dinv of
 // its column (one rounding), or times ds when dinv is nullptr.
 hipError_t res_uniform(const ResOp& op, const int32_t* rp, const int32_t* ci, const double* va, const double* dinv,
                        bool plain, double ds, void* aux, hipStream_t s);
