@@ -2581,14 +2581,16 @@ int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const
     if (!uniform) {
       // varying values are read from the layout each time: where the solve
       // would read them as codes (2^18 rows and more) those are the better form
+      plan.K = 0;
       if (A->n < kViMinRows) {
+        rop.va = A->va;  // not one value per diagonal: the layout's, once it is filled
+        plan = res_plan(rop, o.variant, pcl != PC_NONE, ctx->cus);
+      }
+      if (plan.K > 0) {
         DiaOp dop;
         rc = dia_operator<double>(ctx, A, folded ? pc : PC_NONE, fdv, ds, &dop);
         if (rc != PBCGS_SUCCESS) return rc;
         rop.va = dop.va;
-        plan = res_plan(rop, o.variant, pcl != PC_NONE, ctx->cus);
-      } else {
-        plan.K = 0;
       }
     }
     if (plan.K > 0) {

@@ -14,6 +14,16 @@ namespace pbcgs {
 
 namespace {
 
+// Rows around a workgroup's own in its windows, each side: beyond these the
+// streamed kernels read such surroundings faster, from the caches.  60
+// iterations, far diagonals beyond inner ones H rows away (ms, streamed /
+// resident): p-BiCGStab on varying values, H = 3,000 / 3,500 / 4,000 / 4,400,
+// 120,000 rows 1.07 / 1.05, 1.07 / 1.09, 1.08 / 1.11, 1.08 / 1.15, 250,000 rows
+// 1.39 / 1.17, 1.39 / 1.23, 1.39 / 1.46, 1.39 / 1.56; BiCGStab on one value per
+// diagonal, 250,000 rows, 3,500 / 4,000 / 4,400, 1.76 / 1.36, 1.72 / 1.79, 1.75 /
+// 1.82.
+constexpr int64_t kResMaxH = 3584;
+
 // Rows per thread that `op` can run with, and its windows: the diagonals other
 // than a far first and last one must lie within H rows, and two windows of
 // 512 K + 2 H doubles must fit the 160 KB of LDS beside the kernel's 2.6 KB.
@@ -33,6 +43,7 @@ bool res_fit(const ResOp& op, int K, bool pc, bool pc16, int maxg, ResPlan* p) {
   const bool far = K > 8 || 2 * all > rows;
   const int64_t H = ((far ? inner : all) + 1) & ~1ll;
   if (K > 8 && G < 2) return false;
+  if (H > kResMaxH) return false;
   if ((int64_t)res_lds(K, 0) + 4 * H * 8 > 160 * 1024 - 4096) return false;
   p->K = K;
   p->G = (int)G;

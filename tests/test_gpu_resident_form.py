@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_1612_01395_amd import solver
-from gpu_util import csr_op, dev_t, require_gpu, say
+from gpu_util import csr_op, dev_t, host, require_gpu, same, say
 from test_gpu_resident import ALG, band
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +101,20 @@ def test_budgets_one_launch_may_hold():
     ops, bs = [op] * 3, [dev_t(np.ones(3000))] * 3
     for m in (200000, 200001):
         assert {i.resident_rows > 0 for i in solver.solve_batched(ops, bs, maxit=m)[1]} == {m == 200000}, m
+
+
+def test_surroundings_a_window_may_hold():
+    """Inner diagonals up to 3,584 rows away; the results are the streamed ones."""
+    require_gpu()
+    n = 40000
+    b = dev_t(np.random.default_rng(6).standard_normal(n))
+    for H, want in ((3072, True), (3584, True), (3586, False)):
+        for values in (False, True):
+            op = csr_op(band(n, [-H - 900, -H, -1, 1, H, H + 900], values))
+            say(f"window H={H} varying={values}")
+            for variant in ("pbicgstab", "bicgstab"):
+                kw = dict(variant=variant, tol=0.0, maxit=6, history=True)
+                x, i = solver.solve(op, b, **kw)
+                y, s = solver.solve(op, b, graph=False, **kw)
+                assert (i.resident_rows > 0) == want, (H, values, variant)
+                assert same(host(x), host(y)) and same(host(i.history), host(s.history)), (H, values, variant)
