@@ -2966,7 +2966,9 @@ template <class V, bool P, bool N> struct HasSpmv2<DiaOpT<V, P, N>> : std::true_
 template <int NPTS, class V> struct HasSpmv2<StencilOp<NPTS, V>> : std::true_type {};
 template <class V, bool VAR> struct HasSpmv2<GridOp<V, VAR>> : std::true_type {};
 template <class Op> struct IsStencil : std::false_type {};
-template <int NPTS, class V> struct IsStencil<StencilOp<NPTS, V>> : std::true_type {};
+template <int NPTS, class V> struct IsStencil<StencilOp<NPTS, V>> : std::true_type {
+  static constexpr int points = NPTS;
+};
 template <class Op> struct HasSpmv4 : std::false_type {};
 template <class V, bool P, bool N> struct HasSpmv4<DiaOpT<V, P, N>> : std::true_type {};
 template <class Op> struct IsDia : std::false_type {};

@@ -675,11 +675,44 @@ struct Driver {
   // 12.7 / 13.7, 200^3 24.9 / 21.9 / 24.4, BiCGStab 170^3 16.1 / 12.5 / 13.1,
   // binary32 130^3 5.5 / 4.8 / 4.8, matrix-free 180^3 32.0 / 27.1 / 28.1.  Where
   // the XCD-contiguous indices are on (binary64 p-BiCGStab up to 2^22 rows) they
-  // do as well (145^3 8.1 / 8.4 / 8.9) and are kept.
+  // do as well (145^3 8.1 / 8.4 / 8.9) and are kept, and up to 2^22 rows so are
+  // 1,024 workgroups where few vectors and a short row mean that the caches hold
+  // the sweep anyway (few_fetches()).
+
+  // Points of the operator's rows (a large number where that is not known).
+  int points() const {
+    if constexpr (IsDia<Op>::value) return op.nd;
+    else if constexpr (IsGrid<Op>::value) return op.npts;
+    else if constexpr (IsStencil<Op>::value) return IsStencil<Op>::points;
+    else return INT32_MAX;
+  }
+  // Up to 2^22 rows, 24 iterations with 1,024 workgroups / R = 4 (ms).  At most
+  // five points: CG 1500^2 1.36 / 1.43, 2000^2 1.80 / 1.99 (constant), 2.48 / 2.59
+  // (per row), BiCGStab 2.96 / 3.21, 4.05 / 4.34, p-CG 1.89 / 2.03, binary32
+  // 2000^2 (40 iterations) 3.21 / 3.54; but BiCGStab with Jacobi as written 2000^2
+  // 4.07 / 3.83, CA-BiCGStab 3.94 / 3.62, and with value codes up to 3 2^20 rows
+  // BiCGStab 1460^2 2.89 / 2.65, 1750^2 3.41 / 3.29, CG 1.90 / 1.80, 2.22 / 2.16.
+  // Constant 7-point: p-CG without Jacobi 130^3 1.22 / 1.29, 145^3 1.75 / 1.78, CG
+  // 145^3 1.98 / 1.77, 160^3 2.01 / 2.10.
+  bool few_fetches() const {
+    if (a.n > 2 * kManyRows) return false;
+    const bool mid = a.n <= kManyRows + kManyRows / 2;
+    if (points() <= 5) {
+      if (MP) return true;
+      if constexpr (std::is_same<Op, DiaViOp>::value) {
+        if (mid) return false;
+      }
+      return !(o.variant == PBCGS_CA_BICGSTAB || (o.variant == PBCGS_BICGSTAB && PC != PC_NONE));
+    }
+    if (!IsStencil<Op>::value || MP) return false;
+    return (o.variant == PBCGS_PIPE_CG && PC == PC_NONE) || (o.variant == PBCGS_CG && !mid);
+  }
+
   bool take_many() {
     const int mode = env_int("PBCGS_MANY", -1);
     if (mode == 0 || ctx->noalloc || ctx->streamed_only || (mode < 0 && a.n <= (a.wg == -2 ? 2 : 1) * kManyRows))
       return false;
+    if (mode < 0 && few_fetches()) return false;
     if (std::getenv("PBCGS_R") || std::getenv("PBCGS_GTARGET")) return false;
     const int R = mode > 0 ? mode : kManyR;
     const int64_t G = ((int64_t)a.n + 256 * (int64_t)R - 1) / (256 * (int64_t)R);
