@@ -346,7 +346,8 @@ int pbcgs_jacobi_dinv(pbcgs_ctx_t ctx, pbcgs_op_t A, double* dinv);
  * 7-point stencil) runs, for every variant but CA-BiCGStab, as one cooperative
  * launch that keeps the Krylov vectors in registers and LDS; p-BiCGStab and
  * BiCGStab with Jacobi as written and p-CG with Jacobi up to 2^20 rows, and
- * diagonals whose values vary up to 2^18 rows.  Same results, bit for bit.
+ * diagonals whose values vary up to 2^18 rows, if all but the first and last
+ * diagonal lie within 3,584 rows.  Same results, bit for bit.
  * opts.check_every does not apply to it: nothing is polled while it runs.
  * opts.flags bits 0, 1, 3 and 4, a maxit above 200,000 (a launch cannot be
  * interrupted), budgets too short to pay for it (maxit < 2 below 2^18 rows,
@@ -355,8 +356,10 @@ int pbcgs_jacobi_dinv(pbcgs_ctx_t ctx, pbcgs_op_t A, double* dinv);
  * refuses or that finds the device busy for about 0.07 s (the solve then
  * starts again from x_0, which the resident launch does not touch; the
  * context's next 16 such solves stream, 32 after a second one in a row).
- * Streamed solves of more than 2^21 rows (binary64 p-BiCGStab: 2^22) launch
- * workgroups of 1,024 rows whatever shape was tuned.
+ * Streamed solves of more than 2^21 rows (binary64 p-BiCGStab, operators of at
+ * most five points but for some methods and forms, and unpreconditioned p-CG
+ * and CG on a constant 7-point stencil: up to 2^22) launch workgroups of 1,024
+ * rows whatever shape was tuned.
  */
 int pbcgs_solve(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* x, const double* dinv,
                 const pbcgs_opts* opts, pbcgs_info* info);
@@ -389,7 +392,13 @@ int pbcgs_solve_noalloc(pbcgs_ctx_t ctx, pbcgs_op_t A, const double* b, double* 
  * options (the batched workload of many small and large systems).  A: HOST
  * array of nsys CSR operators of ctx; b, x: HOST arrays of nsys DEVICE
  * pointers (x[k] holds x_0 on entry, the final iterate on return); infos:
- * HOST array of nsys reports.  Every kernel launch covers all systems: each
+ * HOST array of nsys reports.  When every system fits the resident form (see
+ * pbcgs_solve; one value per diagonal, every diagonal within 2,944 rows, maxit
+ * of at least 8), the batch runs in it: cooperative launches of several
+ * systems, and one ordinary launch for systems of one workgroup (up to 4,096
+ * rows) that find no room there; not where those are more than the compute
+ * units and the systems have fewer than 1,024 rows in the mean.  Else every
+ * kernel launch covers all systems: each
  * workgroup belongs to one system, each system has its own scalars, status,
  * reductions and stopping test, and a system that stops leaves the later
  * launches at once.  Reductions are the same pairwise trees as in
@@ -426,6 +435,11 @@ typedef struct {
  * below; later pbcgs_solve calls on A, or on another operator of the same
  * cache key, with that variant, precision and read path use it (the environment variables PBCGS_R
  * and PBCGS_GTARGET still take precedence).  An unknown variant or precision is PBCGS_ERR_INVALID_ARG.
+ * What is timed are the streamed kernels in launches of at most 1,024
+ * workgroups.  A solve in the resident form, and one launched as workgroups of
+ * 1,024 rows (see pbcgs_solve), has a shape of its own and does not use the
+ * tuned one, though pbcgs_info reports it for the launches around a resident
+ * solve; info.resident_rows and info.workgroups tell which ran.
  * The shape never changes a result: every reduction is the same pairwise
  * tree whatever R is.
  */

@@ -1128,10 +1128,12 @@ struct Driver {
       for (;;) {
         while (!stop && launched < o.maxit && npend < 2) {
           int m = (int)std::min<int64_t>(check, o.maxit - launched);
-          // The first polls of a CSR-stream solve come early: matrices without
-          // diagonals tend to need tens of iterations, and one that needs 16 was
-          // given 64 (200,003 rows, 0.9 -> 0.73 ms).  Elsewhere the two more
-          // chunk boundaries cost more than they save (27-point 50^3 3.5 %).
+          // The first polls of a CSR-stream solve come early: one that needs 10
+          // to 20 iterations was given 64 (5,000 to 10^6 rows 1.02-1.8 times
+          // faster, 200,003 rows 0.92 -> 0.75 ms).  Longer ones come out the same
+          // (22 solves of 55 to 264 iterations on 2-D grids of 30^2 to 150^2
+          // 0.94-1.07 times, geometric mean 1.00).  Elsewhere the two more chunk
+          // boundaries cost more than they save (27-point 50^3 3.5 %).
           if (IsCsr<Op>::value && o.check_every <= 0 && launched < 2 * kFirstChunk) m = std::min(m, kFirstChunk);
           if (rate < 0.0 && o.tol > 0.0 && last_rel > 0.0) {
             const double need = (std::log(o.tol) - std::log(last_rel)) / rate;  // from the last poll

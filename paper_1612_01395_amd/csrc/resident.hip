@@ -84,7 +84,11 @@ ResPlan res_plan(const ResOp& op, int32_t variant, bool pc, int cus) {
     ResPlan p;
     if (!res_fit(op, K, pc, m.pc16, maxg, &p)) continue;
     // Microseconds of an iteration that depend on the shape, fitted to runs
-    // at 41^3, 64^3, 99^3, 100^3 and 150^2: an exchange takes 0.015 us more per
+    // at 41^3, 64^3, 99^3, 100^3 and 150^2 (what fits is taken: 40 iterations,
+    // ms, streamed / resident, of p-BiCGStab with Jacobi as written 64^3 1.16 /
+    // 0.68, 81^3 2.18 / 1.67, 101^3 2.74 / 2.16, its eight-row kernel with 248 to
+    // 298 spilled registers; on varying values 32^3 0.61 / 0.49, 48^3 0.72 / 0.55,
+    // 63^3 0.98 / 0.69, CG with Jacobi 48^3 0.70 / 0.71, 63^3 0.91 / 0.77): an exchange takes 0.015 us more per
     // workgroup, a row per thread 0.23 us (CG) to 0.9 us (p-BiCGStab), twice
     // that with 16 rows (x, and r0, then come from memory).  At 64^3
     // p-BiCGStab takes 14.4 / 11.1 / 13.9 us with K = 2 / 4 / 8, BiCGStab

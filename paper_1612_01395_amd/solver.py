@@ -549,7 +549,8 @@ def tune(A: Operator, b: torch.Tensor, iters: int = 20, **opts) -> dict:
     """Time `iters` iterations for each launch shape (rows-per-wave blocks R)
     and keep the fastest on A, and in the process-wide launch-shape cache,
     for later solves of the same variant and precision; returns the report.  ``index32`` / ``diagonal_layout=False``
-    time the solves on those read paths."""
+    time the solves on those read paths.  Solves in the resident form (``SolveInfo.resident_rows`` > 0) and those
+    launched as workgroups of 1,024 rows have shapes of their own and do not use it."""
     _check_vec(b, A.n, "b")
     o = _opts(**opts)
     r = L.TuneReport()
